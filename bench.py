@@ -51,9 +51,10 @@ HBM_PEAK_GBS = 8000.0
 # Non-packed FP32/FP64 VALU issue rate: 256 CU x 4 SIMD x 16 lanes x 2.4 GHz.
 VALU_PEAK_OPS = 256 * 64 * 2.4e9
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.json")
-KERNEL_SOURCES = ["paper_2512_24685_amd/csrc/sre2_kernels.hip",
-                  "paper_2512_24685_amd/csrc/sre2_geometry.h",
-                  "paper_2512_24685_amd/csrc/sre2_plan.h"]
+# Code of the two-pass kernels, whose counters are stored.
+KERNEL_SOURCES = ["paper_2512_24685_amd/csrc/" + f for f in
+                  ("sre2_pass1.hip", "sre2_pass2.hip", "sre2_twopass.h", "sre2_tile.h",
+                   "sre2_device.h", "sre2_geometry.h", "sre2_plan.h")]
 
 
 
@@ -152,18 +153,20 @@ def roofline(N, form, kind, ms, launches, traffic, evals=1, x0=0, xc=None):
                        frac=round(alu / VALU_PEAK_OPS, 4), alg_ops_per_launch=round(ops / launches),
                        hbm_GBs=round(gbs, 1), hbm_frac=round(gbs / HBM_PEAK_GBS, 4))
         return ent
-    # fused kernel: every value stays on chip; VALU-bound.  The Hermitian
-    # forms run x = 0 as a separate short plain launch, so the work and the
-    # time are taken per evaluation (all launches of the class) rather than
-    # per launch.
-    herm = form.endswith("h")
+    # on-chip kernels: every value stays on chip; VALU-bound.  The plain and
+    # Hermitian forms take half transforms from N = 12 (FP64: 11) on; below,
+    # the Hermitian forms run x = 0 as a separate short plain launch, so the
+    # work and the time are taken per evaluation (all launches of the class)
+    # rather than per launch.
+    half = N >= (11 if form.startswith("fp64") else 12) and not form.startswith("split")
+    herm = form.endswith("h") or half
     nt = N - (1 if herm else 0)
     ops = (4 + 2 * nt + (6 if herm else 5)) * (1 << N) * (1 << nt)
     per_eval_s = ms / 1e3 / evals
     alu = ops / per_eval_s
     return {"bound": "alu", "achieved": round(alu / 1e12, 3), "peak": round(VALU_PEAK_OPS / 1e12, 2),
             "unit": "Tops/s", "frac": round(alu / VALU_PEAK_OPS, 4), "traffic": traffic,
-            "kernel": "k_fused", "avg_launch_us": round(avg_s * 1e6, 2), "launches": launches,
+            "kernel": "k_half" if half else "k_fused", "avg_launch_us": round(avg_s * 1e6, 2), "launches": launches,
             "class_us_per_evaluation": round(per_eval_s * 1e6, 2),
             "alg_ops_per_evaluation": ops}
 

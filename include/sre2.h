@@ -67,7 +67,9 @@ extern "C" {
 
 /* ---- arithmetic forms -------------------------------------------------- */
 /* FP32: f_x and every butterfly in float32; |W|^2 in float32, squared and
- * accumulated in float64 (complex128 input is rounded to complex64 first). */
+ * accumulated in float64 (complex128 input is rounded to complex64 first).
+ * For 12 <= N <= 16 (FP64: 11 <= N <= 15) the shifts x >= 1 run on chip as the
+ * half transforms described at the Hermitian-pair forms below. */
 #define SRE2_FORM_FP32 0
 /* SPLIT_F16: the FP32 form with every group of four butterfly stages replaced
  * by one H_16 = H_2^{(x)4} Kronecker factor on the matrix cores: each FP32
@@ -156,8 +158,9 @@ int sre2_set_row_pairs(sre2_ctx* ctx, int enable);
  * Host-only.  Returns -1 for invalid arguments. */
 int64_t sre2_half_slab_first_shift(int N, int form);
 
-/* Device workspace (bytes) a call with these arguments grows the context to,
- * with the current default scratch limit.  0 for invalid arguments. */
+/* Upper bound of the device workspace (bytes) that calls with these arguments
+ * grow the context to, with the current default scratch limit (an M2 call on
+ * an N that is evaluated on chip takes less).  0 for invalid arguments. */
 size_t sre2_workspace_bytes(int N, int dtype, int form);
 
 /* M2 of one state (Algorithm 1 over all 2^N shifts).

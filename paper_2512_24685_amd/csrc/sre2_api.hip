@@ -5,7 +5,8 @@
 // Launch sequence of sre2_m2 on the caller's stream:
 //   [k_convert]        input -> working precision copy (only if dtype != form's)
 //   k_norm_part        FP64 partial norms + non-finite flags
-//   shift sums         k_tiny | k_fused | per chunk: k_pass1, k_pass2, k_group_sum
+//   shift sums         k_tiny | k_fused | k_half | per chunk: k_pass1, k_pass2,
+//                      k_group_sum
 //   k_sum_part         fixed-range FP64 partial sums of S_x
 //   k_final            S, n, M2 = -log2(S / (2^N n^4)), status
 #include <hip/hip_runtime.h>
@@ -95,6 +96,19 @@ int row_bits(int form, int NS) {
     return is_f64(form) ? pass1_row_bits<double>(NS) : pass1_row_bits<float>(NS);
 }
 int herm_min(int form) { return is_f64(form) ? herm_min_n<double>() : herm_min_n<float>(); }
+// The half transforms take this evaluation (spec: its reduction, null for M2).
+bool half_path(int N, int form, const Spec* spec) {
+    return !is_split(form) && !(spec && spec->kind == kRedHist) &&
+           (is_f64(form) ? half_takes<double>(N) : half_takes<float>(N));
+}
+int half_first(int N, int form) {
+    return is_f64(form) ? half_first_shift<double>(N) : half_first_shift<float>(N);
+}
+// Shifts of [x0, x0 + xc) that go through the two-pass kernels (from x0 on).
+int64_t two_pass_shifts(int N, int form, bool half, int64_t x0, int64_t xc) {
+    if (half) return x0 < half_first(N, form) ? half_first(N, form) - x0 : 0;
+    return N <= fused_max(form) ? 0 : xc;
+}
 int64_t col_tiles(int N, int form, bool herm) {
     return is_f64(form) ? pass2_col_tiles<double>(N, herm) : pass2_col_tiles<float>(N, herm);
 }
@@ -310,12 +324,13 @@ int64_t slab_need(int N, int form, bool pairs, int64_t x0, int64_t xc, size_t li
 // and set ws.scratch, ws.part and ws.limit.  When the device cannot hold the
 // slab, the chunks shrink (halving the limit for this call) down to one
 // shift per chunk.  Chunking never changes a result bit.
-// `pairs`: the call may take the row-pair slabs (the context allows them
-// and the call reduces to M2).
-int ctx_two_pass_ws(sre2_ctx* ctx, int N, int form, int64_t x0, int64_t xc, bool pairs,
+// Row-pair slabs are taken when the context allows them and the call reduces
+// to M2 (spec == nullptr).
+int ctx_two_pass_ws(sre2_ctx* ctx, int N, int form, int64_t x0, int64_t xc, const Spec* spec,
                     Workspace* ws) {
-    ws->pairs = pairs && ctx->row_pairs;
-    if (N <= fused_max(form)) return SRE2_OK;
+    ws->pairs = spec == nullptr && ctx->row_pairs;
+    xc = two_pass_shifts(N, form, half_path(N, form, spec), x0, xc);
+    if (xc == 0) return SRE2_OK;
     size_t limit = ctx->scratch_limit, need = 0, need_part = 0;
     int rc;
     for (;;) {
@@ -342,6 +357,19 @@ int shift_sums(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int
     if (fault_injected("launch")) return SRE2_EHIP;
     const bool f64 = is_f64(form);
     const int sp = split_kind(form);
+    if (half_path(N, form, spec)) {
+        const int64_t two = two_pass_shifts(N, form, true, x0, xc);
+        if (two) {
+            const int rc = two_pass(tctx, ws, work, N, form, kSlabFull, x0, two, Sx, se, spec, st);
+            if (rc) return rc;
+        }
+        if (xc == two) return SRE2_OK;
+        Timed tm(tctx, st, SRE2_KIND_SHIFT);
+        return hip_status(f64 ? launch_shift_kernel<double>(work, N, true, 0, x0 + two, xc - two,
+                                                            Sx + two, se, Pack{}, spec, st)
+                              : launch_shift_kernel<float>(work, N, true, 0, x0 + two, xc - two,
+                                                           Sx + two, se, Pack{}, spec, st));
+    }
     const int64_t x1 = x0 + xc;
     if (N <= fused_max(form)) {
         const bool herm = is_herm(form) && N >= herm_min(form);
@@ -456,7 +484,7 @@ int m2_one(sre2_ctx* ctx, const void* psi, int N, int dtype, int form, hipStream
            double* partials, const Spec* spec = nullptr) {
     Workspace ws;
     int rc = ctx_common_ws(ctx, N, dtype, form, partials == nullptr, &ws);
-    if (!rc) rc = ctx_two_pass_ws(ctx, N, form, 0, int64_t(1) << N, spec == nullptr, &ws);
+    if (!rc) rc = ctx_two_pass_ws(ctx, N, form, 0, int64_t(1) << N, spec, &ws);
     if (rc) return rc;
     return m2_launch(ctx, ws, psi, N, dtype, form, st, out, partials, spec, false);
 }
@@ -492,6 +520,7 @@ int m2_pack(sre2_ctx* ctx, const void* const* psi, int count, int N, int dtype, 
     }
     const bool f64 = is_f64(form);
     const int sp = split_kind(form);
+    const bool half = half_path(N, form, nullptr);
     const bool herm = is_herm(form) && N >= herm_min(form);
     const int nb = red_blocks(n);
     {
@@ -502,12 +531,15 @@ int m2_pack(sre2_ctx* ctx, const void* const* psi, int count, int N, int dtype, 
     if (fault_injected("launch")) return SRE2_EHIP;
     {
         Timed tm(ctx, st, SRE2_KIND_SHIFT);
+        // the half transforms take every shift of a packed size, 0 included
         const int64_t plain_end = herm ? 1 : n;
-        hipError_t e = f64 ? launch_shift_kernel<double>(nullptr, N, false, false, 0, plain_end,
-                                                         nullptr, nullptr, pk, nullptr, st)
-                           : launch_shift_kernel<float>(nullptr, N, false, sp, 0, plain_end,
-                                                        nullptr, nullptr, pk, nullptr, st);
-        if (e == hipSuccess && herm)
+        hipError_t e = f64 ? launch_shift_kernel<double>(nullptr, N, half, false, 0,
+                                                         half ? n : plain_end, nullptr, nullptr,
+                                                         pk, nullptr, st)
+                           : launch_shift_kernel<float>(nullptr, N, half, sp, 0,
+                                                        half ? n : plain_end, nullptr, nullptr,
+                                                        pk, nullptr, st);
+        if (e == hipSuccess && herm && !half)
             e = f64 ? launch_shift_kernel<double>(nullptr, N, true, false, 1, n - 1, nullptr,
                                                   nullptr, pk, nullptr, st)
                     : launch_shift_kernel<float>(nullptr, N, true, false, 1, n - 1, nullptr,
@@ -545,11 +577,12 @@ int ws_layout(int N, int dtype, int form, bool need_sx, size_t bytes, size_t* ps
         off = up(off + n * sizeof(double));
     }
     if (off > bytes) return SRE2_ESCRATCH;
-    if (N <= fused_max(form)) return SRE2_OK;
+    const int64_t xc = two_pass_shifts(N, form, half_path(N, form, nullptr), 0, (int64_t)n);
+    if (xc == 0) return SRE2_OK;
     // the largest chunks whose slab and partials fit what is left
     size_t lim = bytes - off, need = 0, need_part = 0;
     for (;;) {
-        const int64_t cs = slab_need(N, form, true, 0, (int64_t)n, lim, &need, &need_part);
+        const int64_t cs = slab_need(N, form, true, 0, xc, lim, &need, &need_part);
         const size_t pb = up(need_part * sizeof(double));
         if (off + pb + need <= bytes) {
             *part_off = off;
@@ -729,7 +762,7 @@ int sre2_partials(sre2_ctx* ctx, const void* psi, int N, int dtype, int form, in
     const hipStream_t st = (hipStream_t)stream;
     Workspace ws;
     rc = ctx_common_ws(ctx, N, dtype, form, false, &ws);
-    if (!rc) rc = ctx_two_pass_ws(ctx, N, form, x_begin, x_count, true, &ws);
+    if (!rc) rc = ctx_two_pass_ws(ctx, N, form, x_begin, x_count, nullptr, &ws);
     if (rc) return rc;
     const void* work = nullptr;
     rc = stage_input(ctx, ws, psi, N, dtype, form, st, &work);

@@ -72,18 +72,37 @@ constexpr int kMaxNAll = 26;
 #define SRE2_F64_P2_COLS 3
 #endif
 
+// On-chip half transforms (k_half): N from HMIN to HMAX.  HMIN: one wave holds
+// 2^(N-1) values (below it launches dominate and several shifts share a tile).
+// HMAX: the half transform fills the register file of a CU (1024 threads of
+// 64 or 512 of 128 value registers) and its real parts 128 KiB of LDS.
+#ifndef SRE2_F32_HALF_MIN
+#define SRE2_F32_HALF_MIN 12
+#endif
+#ifndef SRE2_F64_HALF_MIN
+#define SRE2_F64_HALF_MIN 11
+#endif
+#ifndef SRE2_F32_HALF_MAX
+#define SRE2_F32_HALF_MAX 16
+#endif
+#ifndef SRE2_F64_HALF_MAX
+#define SRE2_F64_HALF_MAX 15
+#endif
+
 template <typename Real> struct Tune;
 template <> struct Tune<float> {
     static constexpr int RBF = SRE2_F32_RB_FUSED, FMIN = SRE2_F32_FUSED_MIN;
     static constexpr int FMAX = SRE2_F32_FUSED_MAX, ROW = SRE2_F32_ROW;
     static constexpr int RB1 = SRE2_F32_RB1, RB2 = SRE2_F32_RB2, P2MIN = SRE2_F32_P2_MIN;
     static constexpr int P2COLS = SRE2_F32_P2_COLS;
+    static constexpr int HMIN = SRE2_F32_HALF_MIN, HMAX = SRE2_F32_HALF_MAX;
 };
 template <> struct Tune<double> {
     static constexpr int RBF = SRE2_F64_RB_FUSED, FMIN = SRE2_F64_FUSED_MIN;
     static constexpr int FMAX = SRE2_F64_FUSED_MAX, ROW = SRE2_F64_ROW;
     static constexpr int RB1 = SRE2_F64_RB1, RB2 = SRE2_F64_RB2, P2MIN = SRE2_F64_P2_MIN;
     static constexpr int P2COLS = SRE2_F64_P2_COLS;
+    static constexpr int HMIN = SRE2_F64_HALF_MIN, HMAX = SRE2_F64_HALF_MAX;
 };
 
 // Row bits of pass 1 for a slab of NS bits (NS = N, or N - 1 in the
@@ -153,6 +172,21 @@ constexpr int fused_rb(int N, bool split) {
            (!split && fused_half<Real>(N)
                 ? (sizeof(Real) == 4 ? SRE2_F32_FUSED_HALF_RB : SRE2_F64_FUSED_HALF_RB)
                 : 0);
+}
+// Registers (log2 of complex values) per thread of a half transform.  FP32: 32
+// values (16: 174 against 163 us at N = 14).  FP64: 16 values up to N = 13
+// (69 against 76 us with 32 there); 32 above, which saves a round where the
+// LDS leaves two or one workgroup per CU anyway (N = 14 283 against 306 us,
+// N = 15 1.55 against 1.76 ms).
+template <typename Real>
+constexpr int half_rb(int N) {
+    return sizeof(Real) == 4 ? 5 : (N <= 13 ? 4 : 5);
+}
+// First shift the half transforms take: 0, or 1 for FP32 sizes above the
+// fused range, whose shift 0 keeps the stage order of the two passes.
+template <typename Real>
+constexpr int half_first(int N) {
+    return sizeof(Real) == 4 && N > Tune<Real>::FMAX ? 1 : 0;
 }
 template <typename Real>
 constexpr int pass2_tb(int H) {

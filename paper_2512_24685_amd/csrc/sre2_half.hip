@@ -1,0 +1,262 @@
+// sre2_half.hip - on-chip half transforms: S_x of whole shifts, 11 <= N <= 16
+// (FP32) / 15 (FP64), for every form but the split ones.
+//
+// For x != 0, f_x(k ^ x) = conj f_x(k) (the summand of Eq. 3 at k and k ^ x),
+// so with hb a set bit of x the transform A of f_x over the half space
+// k_hb = 0 holds every Pauli expectation of the shift: W_x(z) is 2 Re A or
+// 2i Im A, and S_x = 16 sum (Re^4 + Im^4).  Shift 0 has no such pairing, but
+// f_0 = |psi|^2 is real: the two halves k_hb = 0 and 1 are carried as the real
+// and imaginary part of one complex transform, and one last stage A.re +- A.im
+// gives W_0.  Its stages run in the order of the plain transform of 2^N
+// values (top five bits, low five, the rest upwards), so that W_0, a quarter
+// of a Haar state's S, keeps its bits.
+//
+// A workgroup holds one half transform of 2^(N-1) complex values in registers
+// and transposes it between rounds through an LDS buffer of one real part
+// (2^(N-1) floats or doubles), first the real parts, then the imaginary ones.
+// That buffer is what sets the occupancy: at N = 14 a complex buffer leaves
+// two workgroups (2 waves per SIMD) on a CU and a real one four, and the
+// kernel takes 163 us instead of 193 (the full transforms of k_fused, which
+// it replaces: 450 us); the same buffer lets N = 15 and 16 (FP64: 14 and 15)
+// stay on chip at all, where the two passes through HBM moved 8 (16) bytes
+// per Pauli string (N = 16 FP32: 6.9 ms before, 4.2 ms here; FP64 N = 15:
+// 5.0 ms before, 1.55 ms).  The bound is the VALU: N - 1 additions, the
+// product (2) and the term (3) per Pauli string, 0.13 ms at N = 14.
+//
+// Measured and not taken (N = 14 FP32): keeping psi[k] and psi[k ^ x] in
+// registers over 8 or 32 shifts that differ in register bits only (no loads
+// after the first; two waves per SIMD for the registers): 170-176 us; 16
+// values per thread instead of 32: 174 us.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <type_traits>
+#include <utility>
+
+#include "sre2_plan.h"
+#include "sre2_geometry.h"
+#include "sre2_internal.h"
+#include "sre2_device.h"
+
+namespace sre2 {
+
+namespace {
+
+// conj(a) * b, both parts fused (no identity between f_x(k) and f_x(k ^ x)
+// is needed here).
+template <typename C>
+__device__ __forceinline__ C cmul_conj_f(C a, C b) {
+    C r;
+    r.x = a.x * b.x + a.y * b.y;
+    r.y = a.x * b.y - a.y * b.x;
+    return r;
+}
+
+// One part (0: re, 1: im) of the registers to (PUT) or from a padded buffer
+// of reals.  Slots are 4 or 8 bytes: with pad<5> 32 consecutive lanes hit 32
+// distinct slots modulo 32, free of conflicts for both.  ds_read / ds_write
+// offsets are 16 bits: slots above kLdsSplit bytes take a second base.
+constexpr uint32_t kLdsSplit = 32768;
+template <bool PUT, int PART, int RB, uint32_t REG, uint32_t LPERM, uint32_t WAVE, typename Real,
+          typename C>
+__device__ __forceinline__ void lds_part(Real* lds, C (&v)[1 << RB]) {
+    constexpr int SB = 5;
+    char* b = reinterpret_cast<char*>(lds) +
+              pad16<SB>(thread_base<LPERM, WAVE>()) * (uint32_t)sizeof(Real);
+    char* b2 = b + kLdsSplit;
+#pragma unroll
+    for (int i = 0; i < (1 << RB); ++i) {
+        const uint32_t off = pad<SB>(pdep((uint32_t)i, REG)) * (uint32_t)sizeof(Real);
+        Real* p = reinterpret_cast<Real*>(off >= kLdsSplit ? b2 + (off - kLdsSplit) : b + off);
+        if constexpr (PUT)
+            *p = PART ? v[i].y : v[i].x;
+        else
+            (PART ? v[i].y : v[i].x) = *p;
+    }
+}
+
+// Rounds J .. nrounds - 1 of the half transform of NT bits.
+template <typename Real, int NT, int RB, int J>
+struct HalfRunner {
+    using C = typename CT<Real>::T;
+    static constexpr Plan P = make_plan(NT, RB, 5, 0, NT);
+    static constexpr int NV = P.nrounds < 2 ? 1 : (int)pad_rt((1u << NT) - 1u, 5) + 1;
+    __device__ __forceinline__ static void run(Real* lds, C (&v)[1 << RB]) {
+        if constexpr (J < P.nrounds) {
+            constexpr Round a = P.r[J - 1];
+            constexpr Round c = P.r[J];
+            __syncthreads();  // previous readers of the buffer are done
+            lds_part<true, 0, RB, a.reg, a.lperm, a.wave>(lds, v);
+            __syncthreads();
+            lds_part<false, 0, RB, c.reg, c.lperm, c.wave>(lds, v);
+            __syncthreads();
+            lds_part<true, 1, RB, a.reg, a.lperm, a.wave>(lds, v);
+            __syncthreads();
+            lds_part<false, 1, RB, c.reg, c.lperm, c.wave>(lds, v);
+            butterflies<RB, c.reg, c.bfly>(v);
+            HalfRunner<Real, NT, RB, J + 1>::run(lds, v);
+        }
+    }
+};
+
+// Sum over the 64 lanes of a wave: DPP exchanges inside each row of 16 lanes
+// (XOR partners 1, 2, 7, 15: every lane ends with the row's sum), then the
+// four rows in order.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double read_lane(double v, int l) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+    return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
+}
+
+// Waves per SIMD asked of the compiler: with 64 registers of values per thread
+// four fit (128 registers each), with 128 (FP64 N = 14, 15) two.
+template <typename Real>
+__host__ __device__ constexpr int half_waves_per_simd(int rb) {
+    return (1 << rb) * (int)sizeof(Real) > 128 ? 2 : 4;
+}
+
+// Block b of the grid takes shift x_begin + b.
+template <typename Real, int NT, int RB, bool GEN>
+__global__ __launch_bounds__(1 << (NT - RB))
+__attribute__((amdgpu_waves_per_eu(half_waves_per_simd<Real>(RB))))
+void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin,
+            double* __restrict__ S_out, const Pack pk, const Spec sp) {
+    using C = typename CT<Real>::T;
+    using HR = HalfRunner<Real, NT, RB, 1>;
+    constexpr int N = NT + 1;
+    constexpr int NW = (1 << (NT - RB)) / 64;
+    constexpr int NE = 1 << RB;
+    constexpr Round r0 = HR::P.r[0];
+    // bit of k that packs the halves of shift 0: the one the plain transform
+    // (top five bits, low five, the rest upwards) takes last
+    constexpr uint32_t HB0 = N - 6;
+    __shared__ Real lds[HR::NV];
+    __shared__ double red[NW];
+    if (pk.count) {
+        psi = (const C*)pk.psi[blockIdx.y];
+        S_out = pk_sx(pk.ws[blockIdx.y], N) + x_begin;
+    }
+    const auto rs = buf_rsrc(psi, (uint32_t)sizeof(C) << N);
+    const uint32_t x = (uint32_t)x_begin + blockIdx.x;
+    const bool zero = x == 0;
+    // element e -> k = insert0(e, hb), and the pair k ^ xl; insert0 and the XOR
+    // act on disjoint bits of the thread's and the register's part of e, so
+    // the register's part of an address is uniform (a scalar offset)
+    const uint32_t xl = zero ? 1u << HB0 : x;
+    const uint32_t hb = 31u - __clz(xl);
+    const uint32_t R = insert0(r0.reg, hb);
+    const uint32_t kb = insert0(thread_base<r0.lperm, r0.wave>(), hb);
+    const uint32_t vb = kb ^ (xl & ~R), xr = xl & R;
+    C v[NE];
+    if (zero) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const uint32_t kr = insert0(pdep((uint32_t)i, r0.reg), hb);
+            const C a = load_at<C>(rs, vb, kr ^ xr), c = load_at<C>(rs, kb, kr);
+            v[i].x = cmul_conj_a(c, c).x;
+            v[i].y = cmul_conj_a(a, a).x;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const uint32_t kr = insert0(pdep((uint32_t)i, r0.reg), hb);
+            v[i] = cmul_conj_f(load_at<C>(rs, vb, kr ^ xr), load_at<C>(rs, kb, kr));
+        }
+    }
+    butterflies<RB, r0.reg, r0.bfly>(v);
+    HR::run(lds, v);
+    double acc = 0.0;
+    if (zero) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const Real a = v[i].x + v[i].y, c = v[i].x - v[i].y;
+            if constexpr (GEN) {
+                acc += gen_term<Real>(a * a, sp, Real(0), nullptr) +
+                       gen_term<Real>(c * c, sp, Real(0), nullptr);
+            } else {
+                const double da = (double)(a * a), dc = (double)(c * c);
+                acc += da * da + dc * dc;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            if constexpr (GEN)
+                acc += gen_terms<Real, true>(v[i], sp, Real(0), nullptr);
+            else
+                acc += abs4h(v[i]);
+        }
+        if constexpr (!GEN) acc *= 16.0;
+    }
+    acc = wave_sum(acc);
+    if constexpr (NW == 1) {
+        if (threadIdx.x == 0) S_out[blockIdx.x] = acc;
+    } else {
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) t += red[w];
+            S_out[blockIdx.x] = t;
+        }
+    }
+}
+
+template <typename Real, int N, bool GEN>
+hipError_t launch_half_n(const void* psi, int64_t x0, int64_t xc, double* S, const Pack& pk,
+                         const Spec& sp, hipStream_t st) {
+    using C = typename CT<Real>::T;
+    constexpr int RB = half_rb<Real>(N);
+    hipLaunchKernelGGL((k_half<Real, N - 1, RB, GEN>),
+                       dim3((unsigned)xc, (unsigned)(pk.count ? pk.count : 1)),
+                       dim3(1 << (N - 1 - RB)), 0, st, (const C*)psi, x0, S, pk, sp);
+    return hipGetLastError();
+}
+
+template <typename Real, bool GEN, int... Ns>
+hipError_t dispatch_half(int N, const void* psi, int64_t x0, int64_t xc, double* S,
+                         const Pack& pk, const Spec& sp, hipStream_t st,
+                         std::integer_sequence<int, Ns...>) {
+    hipError_t e = hipErrorInvalidValue;
+    ((N == Ns + Tune<Real>::HMIN
+          ? (e = launch_half_n<Real, Ns + Tune<Real>::HMIN, GEN>(psi, x0, xc, S, pk, sp, st), 0)
+          : 0),
+     ...);
+    return e;
+}
+
+}  // namespace
+
+template <typename Real>
+hipError_t launch_half(const void* psi, int N, int64_t x0, int64_t xc, double* S, const Pack& pk,
+                       const Spec* sp, hipStream_t st) {
+    if (N < Tune<Real>::HMIN || N > Tune<Real>::HMAX || xc < 1 || x0 < (half_first<Real>(N)) ||
+        x0 + xc > ((int64_t)1 << N))
+        return hipErrorInvalidValue;
+    constexpr auto ns = std::make_integer_sequence<int, Tune<Real>::HMAX - Tune<Real>::HMIN + 1>{};
+    if (sp) return dispatch_half<Real, true>(N, psi, x0, xc, S, pk, *sp, st, ns);
+    return dispatch_half<Real, false>(N, psi, x0, xc, S, pk, Spec{}, st, ns);
+}
+template hipError_t launch_half<float>(const void*, int, int64_t, int64_t, double*, const Pack&,
+                                       const Spec*, hipStream_t);
+template hipError_t launch_half<double>(const void*, int, int64_t, int64_t, double*, const Pack&,
+                                        const Spec*, hipStream_t);
+
+}  // namespace sre2

@@ -31,6 +31,18 @@ int64_t pass2_col_tiles(int N, bool herm) {
     const int tb = HT >= 1 && HT <= Prec<Real>::MAXTB ? pass2_tb<Real>(HT) : 0;
     return tb > 0 ? (int64_t)1 << (NS - tb) : 0;
 }
+template <typename Real>
+bool half_takes(int N) {
+    return N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX;
+}
+template <typename Real>
+int half_first_shift(int N) {
+    return half_first<Real>(N);
+}
+template bool half_takes<float>(int);
+template bool half_takes<double>(int);
+template int half_first_shift<float>(int);
+template int half_first_shift<double>(int);
 template int max_n<float>();
 template int max_n<double>();
 template int fused_max_n<float>();
