@@ -82,8 +82,7 @@ def slab_ranges(N: int, form: str, x0: int, xc: int):
     shift in pass 2, shifts).  Shifts below 2^L take the full slab of 2^N
     values; above (from `sre2_half_slab_first_shift`), the Hermitian-pair
     forms and (row pairs, on by default) the plain and split forms take half
-    slabs of 2^(N-1) values; the row pairs still transform 2^N values per
-    shift in pass 2."""
+    slabs of 2^(N-1) values, which pass 2 transforms as they are."""
     import paper_2512_24685_amd as sre2
 
     herm = form.endswith("h")
@@ -96,7 +95,7 @@ def slab_ranges(N: int, form: str, x0: int, xc: int):
     lo = max(0, min(x0 + xc, first) - x0)
     out = [(1 << N, Lf, 1 << N, lo)] if lo else []
     if xc > lo:
-        out.append((1 << (N - 1), Lh, 1 << (N - 1) if herm else 1 << N, xc - lo))
+        out.append((1 << (N - 1), Lh, 1 << (N - 1), xc - lo))
     return out
 
 
@@ -109,10 +108,9 @@ def alg_totals(N: int, form: str, kind: str, x0: int, xc: int):
     VALU ops per value: pass 1 = 4 (conj product) + 2 per butterfly stage
     over the L row bits, per slab value; pass 2 = 2 per stage over the
     remaining bits + 5 (|W|^2, square in FP64, FP64 add), per transformed
-    value; Hermitian pass 2: + 1 (two squares).
+    value; half slabs: + 1 (two squares).
     """
     eb = 16 if form.startswith("fp64") else 8
-    herm = form.endswith("h")
     by = ops = 0
     for vals, L, tvals, n in slab_ranges(N, form, x0, xc):
         by += eb * vals * n
@@ -120,7 +118,7 @@ def alg_totals(N: int, form: str, kind: str, x0: int, xc: int):
             ops += (4 + 2 * L) * vals * n
         elif kind == "pass2":
             nt = tvals.bit_length() - 1
-            ops += (2 * (nt - L) + (6 if herm and vals < 1 << N else 5)) * tvals * n
+            ops += (2 * (nt - L) + (6 if vals < 1 << N else 5)) * tvals * n
         else:
             raise ValueError(kind)
     return by, ops
@@ -146,7 +144,7 @@ def roofline(N, form, kind, ms, launches, traffic, evals=1, x0=0, xc=None):
                "alg_bytes_per_launch": round(by / launches), "alu_tops": round(alu / 1e12, 3),
                "alu_frac": round(alu / VALU_PEAK_OPS, 4)}
         if alu / VALU_PEAK_OPS > gbs / HBM_PEAK_GBS:
-            # closer to its arithmetic roof than to HBM (the row-pair pass 2):
+            # closer to its arithmetic roof than to HBM:
             # report it against the VALU issue rate, HBM figures beside
             ent.update(bound="alu", achieved=round(alu / 1e12, 3),
                        peak=round(VALU_PEAK_OPS / 1e12, 2), unit="Tops/s",

@@ -131,30 +131,30 @@ int sre2_destroy(sre2_ctx* ctx);
 int sre2_set_scratch_limit(sre2_ctx* ctx, size_t bytes);
 
 /* Row pairs of the plain and split forms (default on).  Pass 1 of the
- * two-pass path (N >= 15 in FP32, N >= 14 in FP64) transforms the rows of a
- * shift's 2^L x 2^(N-L) slab over their low L bits (Algorithm 1's transform
- * split into rows and columns).  Because f_x(k XOR x) = conj f_x(k) (the
- * summand of Eq. 3 at k and k XOR x), row r XOR (x >> L) of that slab is
- * row r with its L-bit input XOR-permuted and conjugated; for x >= 2^L the
- * library stores only the half of the rows whose bit j is clear (j a set bit
- * of x >> L) and pass 2 rebuilds the other half by sign flips, which halves
- * the memory traffic and the pass-1 work of those shifts.  In the plain
- * FP32 / FP64 forms the rebuilt rows equal those of the full slab bit for
- * bit, so every S_x, S and M2 is identical either way; in the split forms
- * (whose H_16 products on the matrix cores sum in an order the permutation
- * does not preserve) they are the exact images of the computed stored rows,
- * so results differ from the full slab's by rounding only, within the same
- * error bound.  enable = 0 keeps the full slab (for comparison).  The general
- * index and the spectrum (sre2_sre, sre2_pauli_spectrum) always take the
- * full slab.  Errors: SRE2_EINVAL (ctx == NULL). */
+ * two-pass path transforms the rows of a shift's 2^L x 2^(N-L) slab over their
+ * low L bits (Algorithm 1's transform split into rows and columns).  Because
+ * f_x(k XOR x) = conj f_x(k) (the summand of Eq. 3 at k and k XOR x), row
+ * r XOR (x >> L) of that slab is row r with its L-bit input XOR-permuted and
+ * conjugated; for x >= 2^L the library stores only the half of the rows whose
+ * bit j is clear (j the top set bit of x >> L).  With A their column
+ * transform, the values of the shift are 2 Re A and 2i Im A, which halves the
+ * memory traffic and the work of those shifts.  enable = 0 keeps the full slab
+ * (for comparison): the plain FP32 / FP64 forms then transform its two halves
+ * apart and combine them last, and every S_x, S and M2 is identical either
+ * way, bit for bit; in the split forms (whose H_16 products on the matrix
+ * cores sum in an order the permutation does not preserve) results differ
+ * from the full slab's by rounding only, within the same error bound.  The
+ * general index (sre2_sre) takes the row pairs too; the spectrum
+ * (sre2_pauli_spectrum) always takes the full slab.  Sizes evaluated on chip
+ * have no slab.  Errors: SRE2_EINVAL (ctx == NULL). */
 int sre2_set_row_pairs(sre2_ctx* ctx, int enable);
 
 /* First shift x of an N-qubit evaluation that takes a half slab in the
  * two-pass path with the default settings (Hermitian pair; row pairs, which
- * start at 2^L, or in the plain forms where x >> L has a register row bit
- * of the pass-2 tile when that tile is a half-LDS one: 2^(L + 5) at N = 22
- * and 24 in FP32);
- * shifts below it take the full slab.  2^N when N uses the fused kernel.
+ * start at 2^L, or in the plain forms where x >> L reaches the upper row bits
+ * when the column transform of a full slab takes a tile above 64 KiB:
+ * 2^(L + 5) at N = 22 and 24 in FP32); shifts below it take the full slab.
+ * 2^N when N uses the fused kernel.
  * Host-only.  Returns -1 for invalid arguments. */
 int64_t sre2_half_slab_first_shift(int N, int form);
 

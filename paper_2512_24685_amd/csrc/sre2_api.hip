@@ -109,8 +109,8 @@ int64_t two_pass_shifts(int N, int form, bool half, int64_t x0, int64_t xc) {
     if (half) return x0 < half_first(N, form) ? half_first(N, form) - x0 : 0;
     return N <= fused_max(form) ? 0 : xc;
 }
-int64_t col_tiles(int N, int form, bool herm) {
-    return is_f64(form) ? pass2_col_tiles<double>(N, herm) : pass2_col_tiles<float>(N, herm);
+int64_t col_tiles(int N, int form, int slab) {
+    return is_f64(form) ? pass2_col_tiles<double>(N, slab) : pass2_col_tiles<float>(N, slab);
 }
 
 // Two-pass chunking: shifts per chunk (power of two) and column groups per shift.
@@ -119,9 +119,10 @@ struct Chunking {
     int P = 1;
 };
 
-// Slab bits of one shift and pass-1 row bits of a slab kind (kSlabFull,
-// kSlabHerm, kSlabPairs).
-int slab_bits(int N, int slab) { return N - (slab == kSlabFull ? 0 : 1); }
+// Slab bits of one shift and pass-1 row bits of a slab kind.
+int slab_bits(int N, int slab) {
+    return N - (slab == kSlabHerm || slab == kSlabPairs ? 1 : 0);
+}
 int slab_rows(int form, int N, int slab) {
     return row_bits(form, slab == kSlabHerm ? N - 1 : N);
 }
@@ -137,42 +138,47 @@ Chunking chunking(int N, int form, int slab, int64_t x_count, size_t limit) {
     c.cs = cs;
     // Column groups per shift depend on (N, form) only - never on the chunk
     // size - so the order of the FP64 partial sums, and hence every result
-    // bit, is independent of the scratch limit.  The row pairs keep the
-    // full slab's pass-2 tiles.  At most 16 groups: each workgroup then loops
+    // bit, is independent of the scratch limit.  At most 16 groups: each workgroup then loops
     // over several column tiles and loads the next during each transform
     // (N = 20: 3 % faster than 64 groups, 1-2 % than 32).
-    const int64_t tiles = col_tiles(N, form, slab == kSlabHerm);
+    const int64_t tiles = col_tiles(N, form, slab);
     int P = 1;
     while (P < 16 && P * 2 <= tiles) P *= 2;
     c.P = P;
     return c;
 }
 
+// Slab kind of the shifts of a two-pass evaluation that need not take the
+// full slab (spec: its reduction, null for M2; pairs: row pairs allowed).  The
+// histogram keeps the plain transform's stage order, as its counts depend on
+// every rounding; so do the reductions that have no comparison kernel when
+// row pairs are off.
+int high_slab(int form, bool pairs, const Spec* spec) {
+    if (is_herm(form)) return kSlabHerm;
+    if (spec && spec->kind == kRedHist) return kSlabFull;
+    if (pairs) return kSlabPairs;
+    return spec || is_split(form) ? kSlabFull : kSlabBoth;
+}
+
 // The shifts [x0, x0 + xc) of a two-pass evaluation split into at most two
-// ranges by slab kind: the full slab below 2^L, the half slab (Hermitian
-// pair; row pairs of the plain and split M2 forms when `pairs`) above.
+// ranges by slab kind: the full slab below 2^L, `high` above.
 struct SlabRange {
     int slab;
     int64_t x0, xc;
 };
-int slab_ranges(int N, int form, bool pairs, int64_t x0, int64_t xc, SlabRange* out) {
+int slab_ranges(int N, int form, int high, int64_t x0, int64_t xc, SlabRange* out) {
     const int64_t x1 = x0 + xc;
-    int half = kSlabFull;
-    if (is_herm(form))
-        half = kSlabHerm;
-    else if (pairs)
-        half = kSlabPairs;
     int64_t split = x1;
-    if (half != kSlabFull) {
+    if (high != kSlabFull) {
         const int64_t lim =
-            half == kSlabHerm ? int64_t(1) << slab_rows(form, N, half)
+            high == kSlabHerm ? int64_t(1) << slab_rows(form, N, high)
             : is_f64(form)    ? pair_first_shift<double>(N, 0)
                               : pair_first_shift<float>(N, split_kind(form));
         split = x0 > lim ? x0 : (x1 < lim ? x1 : lim);
     }
     int k = 0;
     if (split > x0) out[k++] = SlabRange{kSlabFull, x0, split - x0};
-    if (x1 > split) out[k++] = SlabRange{half, split, x1 - split};
+    if (x1 > split) out[k++] = SlabRange{high, split, x1 - split};
     return k;
 }
 
@@ -262,16 +268,9 @@ int two_pass(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int f
     const bool f64 = is_f64(form);
     const int split = split_kind(form);
     const Chunking ch = chunking(N, form, slab, xc, ws.limit);
-    // row pairs: a chunk stays inside one block of 2^L shifts (one row part
-    // x >> L per launch, so every workgroup takes the same specialisation)
-    const int64_t blk = slab == kSlabPairs ? int64_t(1) << slab_rows(form, N, slab) : 0;
     for (int64_t c0 = 0, cs = 0; c0 < xc; c0 += cs) {
         // a short last chunk keeps the same column grouping
         cs = xc - c0 < ch.cs ? xc - c0 : ch.cs;
-        if (blk) {
-            const int64_t to_edge = blk - ((x0 + c0) & (blk - 1));
-            cs = cs < to_edge ? cs : to_edge;
-        }
         hipError_t e;
         {
             Timed tm(tctx, st, SRE2_KIND_PASS1);
@@ -302,14 +301,14 @@ int two_pass(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int f
 // *need = slab bytes and *need_part = column-group partials (doubles) for
 // the largest chunk shape of its slab ranges.  Returns the largest chunk
 // (shifts).
-int64_t slab_need(int N, int form, bool pairs, int64_t x0, int64_t xc, size_t limit,
+int64_t slab_need(int N, int form, int high, int64_t x0, int64_t xc, size_t limit,
                   size_t* need, size_t* need_part) {
     const int elem = elem_bytes(work_dtype(form));
     *need = 0;
     *need_part = 0;
     int64_t cs_max = 0;
     SlabRange rg[2];
-    const int nr = slab_ranges(N, form, pairs, x0, xc, rg);
+    const int nr = slab_ranges(N, form, high, x0, xc, rg);
     for (int i = 0; i < nr; ++i) {
         const Chunking c = chunking(N, form, rg[i].slab, rg[i].xc, limit);
         const size_t b = (size_t)c.cs * (size_t(1) << slab_bits(N, rg[i].slab)) * elem;
@@ -324,17 +323,17 @@ int64_t slab_need(int N, int form, bool pairs, int64_t x0, int64_t xc, size_t li
 // and set ws.scratch, ws.part and ws.limit.  When the device cannot hold the
 // slab, the chunks shrink (halving the limit for this call) down to one
 // shift per chunk.  Chunking never changes a result bit.
-// Row-pair slabs are taken when the context allows them and the call reduces
-// to M2 (spec == nullptr).
+// `spec`: the call's reduction (null for M2).
 int ctx_two_pass_ws(sre2_ctx* ctx, int N, int form, int64_t x0, int64_t xc, const Spec* spec,
                     Workspace* ws) {
-    ws->pairs = spec == nullptr && ctx->row_pairs;
+    ws->pairs = ctx->row_pairs;
+    const int high = high_slab(form, ws->pairs, spec);
     xc = two_pass_shifts(N, form, half_path(N, form, spec), x0, xc);
     if (xc == 0) return SRE2_OK;
     size_t limit = ctx->scratch_limit, need = 0, need_part = 0;
     int rc;
     for (;;) {
-        const int64_t cs_max = slab_need(N, form, ws->pairs, x0, xc, limit, &need, &need_part);
+        const int64_t cs_max = slab_need(N, form, high, x0, xc, limit, &need, &need_part);
         rc = ensure(&ctx->scratch, &ctx->scratch_bytes, need);
         if (rc != SRE2_ENOMEM || cs_max <= 1) break;
         limit = need / 2;
@@ -395,7 +394,7 @@ int shift_sums(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int
         return SRE2_OK;
     }
     SlabRange rg[2];
-    const int nr = slab_ranges(N, form, ws.pairs && spec == nullptr, x0, xc, rg);
+    const int nr = slab_ranges(N, form, high_slab(form, ws.pairs, spec), x0, xc, rg);
     for (int i = 0; i < nr; ++i) {
         const int rc = two_pass(tctx, ws, work, N, form, rg[i].slab, rg[i].x0, rg[i].xc,
                                 Sx + (rg[i].x0 - x0), se, spec, st);
@@ -582,7 +581,7 @@ int ws_layout(int N, int dtype, int form, bool need_sx, size_t bytes, size_t* ps
     // the largest chunks whose slab and partials fit what is left
     size_t lim = bytes - off, need = 0, need_part = 0;
     for (;;) {
-        const int64_t cs = slab_need(N, form, true, 0, xc, lim, &need, &need_part);
+        const int64_t cs = slab_need(N, form, high_slab(form, true, nullptr), 0, xc, lim, &need, &need_part);
         const size_t pb = up(need_part * sizeof(double));
         if (off + pb + need <= bytes) {
             *part_off = off;
@@ -691,7 +690,8 @@ size_t sre2_workspace_bytes(int N, int dtype, int form) {
     if (work_dtype(form) != dtype) b += n * (size_t)elem_bytes(work_dtype(form));
     if (N > fused_max(form)) {
         size_t slab = 0, part = 0;
-        slab_need(N, form, true, 0, (int64_t)n, kDefaultScratchLimit, &slab, &part);
+        slab_need(N, form, high_slab(form, true, nullptr), 0, (int64_t)n, kDefaultScratchLimit, &slab,
+                  &part);
         b += slab + part * sizeof(double);
     }
     return b;
@@ -861,7 +861,7 @@ int sre2_chunking(sre2_ctx* ctx, int N, int form, int64_t* shifts_per_chunk, int
     // the chunks of the high shifts x >= 2^L, most of an evaluation
     SlabRange rg[2];
     const int64_t n = int64_t(1) << N;
-    const int nr = slab_ranges(N, form, ctx->row_pairs, 0, n, rg);
+    const int nr = slab_ranges(N, form, high_slab(form, ctx->row_pairs, nullptr), 0, n, rg);
     const Chunking ch = chunking(N, form, rg[nr - 1].slab, n, ctx->scratch_limit);
     *shifts_per_chunk = ch.cs;
     *groups = ch.P;
@@ -874,7 +874,7 @@ int64_t sre2_half_slab_first_shift(int N, int form) {
     const int64_t n = int64_t(1) << N;
     if (N <= fused_max(form)) return n;
     SlabRange rg[2];
-    const int nr = slab_ranges(N, form, true, 0, n, rg);
+    const int nr = slab_ranges(N, form, high_slab(form, true, nullptr), 0, n, rg);
     return rg[nr - 1].slab == kSlabFull ? n : rg[nr - 1].x0;
 }
 

@@ -17,7 +17,8 @@ template <> struct CT<double> { using T = double2; };
 // conj(a) * b.  The imaginary part rounds both products before the
 // difference (no fused multiply-add), so that cmul_conj_a(b, a) is exactly
 // conj(cmul_conj_a(a, b)): f_x(k ^ x) = conj f_x(k) then holds bit for bit,
-// which the row-pair slabs of the two-pass path rely on.  The real part may
+// which makes the half slabs of the two-pass path agree with full slabs bit
+// for bit.  The real part may
 // fuse one product: a.x b.x + a.y b.y with either product fused is the same
 // for (a, b) and (b, a), as the same expression fuses the same position
 // (the GPU tests compare row-pair and full-slab results bit for bit).
@@ -40,11 +41,12 @@ __device__ __forceinline__ double abs4(C w) {  // |w|^4 with the square in FP64
 }
 
 // Hermitian-pair form: 16 (Re^4 + Im^4) of one half-space transform value
-// equals the sum of |W|^4 over the two Pauli strings it stands for.
+// equals the sum of |W|^4 over the two Pauli strings it stands for.  The fused
+// square is named, so that every kernel rounds the sum alike.
 template <typename C>
 __device__ __forceinline__ double abs4h(C w) {
     const double a = (double)(w.x * w.x), b = (double)(w.y * w.y);
-    return a * a + b * b;
+    return __builtin_fma(a, a, b * b);
 }
 
 // General reduction of one w = |W|^2 (Spec kinds): the term of the sum in
@@ -158,35 +160,10 @@ __device__ __forceinline__ uint32_t insert0(uint32_t v, uint32_t hb) {
     return ((v >> hb) << (hb + 1)) | (v & ((1u << hb) - 1u));
 }
 
-// Remove bit `b` of `v` (the bits above it move down by one): the inverse
-// of insert0 on values with that bit clear.  Like insert0 it maps disjoint
-// bit sets to disjoint bit sets, so it adds over them.
-__host__ __device__ constexpr uint32_t remove_bit(uint32_t v, int b) {
-    return ((v >> (b + 1)) << b) | (v & ((1u << b) - 1u));
-}
-
 // Row bit left out of a half slab (Hermitian pair, row pairs), for the row
-// part xh = x >> L (nonzero) of a shift x: a set bit of xh, the lowest one
-// inside `pref` when there is one, else the top one.  Pass 1 then builds
-// only the slab rows with that bit clear.
-__device__ __forceinline__ int half_row_bit(uint32_t xh, uint32_t pref) {
-    const uint32_t p = xh & pref;
-    return p ? __builtin_ctz(p) : 31 - __builtin_clz(xh);
-}
-
-// Flip the sign bits of a complex value's parts by the masks mx, my (each
-// 0 or the sign bit of a float, applied to the high word of a double).
-constexpr uint32_t kSign = 0x80000000u;
-__device__ __forceinline__ float2 xor_signs(float2 v, uint32_t mx, uint32_t my) {
-    v.x = __uint_as_float(__float_as_uint(v.x) ^ mx);
-    v.y = __uint_as_float(__float_as_uint(v.y) ^ my);
-    return v;
-}
-__device__ __forceinline__ double2 xor_signs(double2 v, uint32_t mx, uint32_t my) {
-    v.x = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v.x) ^ ((uint64_t)mx << 32));
-    v.y = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v.y) ^ ((uint64_t)my << 32));
-    return v;
-}
+// part xh = x >> L (nonzero) of a shift x: the top set bit of xh.  Pass 1
+// then builds only the slab rows with that bit clear.
+__device__ __forceinline__ int half_row_bit(uint32_t xh) { return 31 - __builtin_clz(xh); }
 
 // Butterflies over the register bits of `bfly` (a subset of `reg`), one tile
 // bit at a time (compile-time recursion keeps every register index constant).

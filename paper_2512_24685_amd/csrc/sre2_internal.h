@@ -74,8 +74,9 @@ template <typename Real> int max_n();
 template <typename Real> int fused_max_n();
 template <typename Real> int pass1_row_bits(int NS);
 template <typename Real> int herm_min_n();
-// Column tiles per shift in pass 2 (upper bound of the column groups P).
-template <typename Real> int64_t pass2_col_tiles(int N, bool herm);
+// Column tiles per shift in pass 2 for a slab kind (upper bound of the column
+// groups P).
+template <typename Real> int64_t pass2_col_tiles(int N, int slab);
 
 // N evaluated on chip by half transforms (all forms but the split ones, all
 // reductions but the histogram), and the first shift they take there (0, or
@@ -102,23 +103,24 @@ hipError_t launch_half(const void* psi, int N, int64_t x0, int64_t xc, double* S
                        const Spec* sp, hipStream_t st);
 // Two-pass slab kinds: the full slab of 2^N values per shift; the Hermitian
 // pair's half slab (2^(N-1) values, rows of pass1_row_bits(N - 1) bits); the
-// row pairs of the plain and split M2 forms (half the rows of the full slab,
-// rows of pass1_row_bits(N) bits; pass 2 rebuilds the other half from them
-// by sign flips: in the plain FP32 / FP64 forms S_x is then bit for bit that
-// of the full slab, in the split forms it differs by rounding only).  The
-// half slabs need x >= 2^L.
+// row pairs of the plain and split forms (half the rows of the full slab,
+// rows of pass1_row_bits(N) bits); a full slab whose two halves pass 2
+// transforms apart (row pairs switched off: S_x of the plain M2 forms bit for
+// bit that of the row pairs).  The last three need x >= 2^L.
 constexpr int kSlabFull = 0;
 constexpr int kSlabHerm = 1;
 constexpr int kSlabPairs = 2;
+constexpr int kSlabBoth = 3;
+// First shift of the row-pair range (shifts below it take the full slab):
+// 2^L, or 2^(L + r) when the plain column transform of a full slab takes a
+// half-LDS tile (r: the lowest register row bit of its plan); 2^N when N is
+// fused.
+template <typename Real>
+int64_t pair_first_shift(int N, int split);
 // Two-pass, one chunk of cs shifts starting at x0: pass 1 writes the
 // row-transformed slabs (cs * 2^N or cs * 2^(N-1) complex values) to
 // `scratch`; pass 2 writes part[s*P + p], the p-th column-group partial of
 // shift x0+s.
-// First shift of the row-pair range (shifts below it take the full slab):
-// 2^L, or 2^(L + r) when the plain pass-2 tile is a half-LDS tile (r: the
-// lowest register row bit of its plan); 2^N when N is fused.
-template <typename Real>
-int64_t pair_first_shift(int N, int split);
 template <typename Real>
 hipError_t launch_pass1(const void* psi, int N, int slab, int split, int64_t x0, int cs,
                         void* scratch, const int* se, hipStream_t st);

@@ -20,8 +20,8 @@
 //                  x >= 2^TB only half its rows: Hermitian pair, row pairs).
 //  sre2_pass2.hip  k_pass2: column transform over the high N-TB bits, |W|^4
 //                  and a per-workgroup FP64 partial sum; nothing is written
-//                  back.  The row-pair form rebuilds the rows pass 1 left
-//                  out, exactly.
+//                  back.  Half slabs are transformed as they are: 2 Re and
+//                  2i Im of the result are the values of the shift.
 // Here:
 //  k_convert / k_norm_part / k_sum_part / k_final: input staging, FP64 norm,
 //              fixed-order FP64 reductions and the logarithm.

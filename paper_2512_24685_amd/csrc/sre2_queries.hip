@@ -25,11 +25,11 @@ int herm_min_n() {
     return Tune<Real>::RBF + 1;
 }
 template <typename Real>
-int64_t pass2_col_tiles(int N, bool herm) {
-    const int NS = N - (herm ? 1 : 0);
-    const int HT = NS - row_bits_of<Real>(NS);
+int64_t pass2_col_tiles(int N, int slab) {
+    const int L = row_bits_of<Real>(slab == kSlabHerm ? N - 1 : N);
+    const int HT = N - L - (slab == kSlabFull ? 0 : 1);
     const int tb = HT >= 1 && HT <= Prec<Real>::MAXTB ? pass2_tb<Real>(HT) : 0;
-    return tb > 0 ? (int64_t)1 << (NS - tb) : 0;
+    return tb > 0 ? (int64_t)1 << (L + HT - tb) : 0;
 }
 template <typename Real>
 bool half_takes(int N) {
@@ -51,7 +51,7 @@ template int pass1_row_bits<float>(int);
 template int pass1_row_bits<double>(int);
 template int herm_min_n<float>();
 template int herm_min_n<double>();
-template int64_t pass2_col_tiles<float>(int, bool);
-template int64_t pass2_col_tiles<double>(int, bool);
+template int64_t pass2_col_tiles<float>(int, int);
+template int64_t pass2_col_tiles<double>(int, int);
 
 }  // namespace sre2
