@@ -6,7 +6,7 @@
 // its own.  Operations, all as HIP kernels on that stream:
 //   * random product state  prod_i (cos(t_i/2)|0> + e^{i p_i} sin(t_i/2)|1>)
 //     (the initial state of the Hamiltonian-quench example);
-//   * two-qubit gates       4x4 unitaries on qubit pairs, index
+//   * two-qubit gates       4x4 unitaries on qubit pairs, several per pass, index
 //     j = bit(q0) + 2 bit(q1) (the brickwork random-circuit example);
 //   * TFIM step             psi <- exp(-i H dt) psi for
 //     H = -J sum_{i=0}^{N-2} Z_i Z_{i+1} - hx sum_i X_i - hz sum_i Z_i (open
@@ -38,58 +38,134 @@ constexpr int kSimMaxN = 26;
 constexpr int kRing = 4;  // snapshot buffers of the pipeline
 
 struct ProductArgs {
-    double c0[kSimMaxN];   // cos(theta_i / 2)
-    double c1r[kSimMaxN];  // Re e^{i phi_i} sin(theta_i / 2)
-    double c1i[kSimMaxN];  // Im
+    double2 f[2 * kSimMaxN];  // qubit i: cos(theta_i / 2), e^{i phi_i} sin(theta_i / 2)
 };
 
-struct Gate {
-    double re[16], im[16];  // row-major U[i][j]
+// One pass over the state for several gates: the gates act inside a tile of
+// tb qubits (the state's other qubits select the tile), which a workgroup
+// holds in LDS.  kTileQubits: 2^11 complex128 = 32 KiB, two workgroups of 512
+// threads per CU at N = 20.  kPassGates: the matrices travel in the kernel
+// arguments (4 KiB).
+#ifndef SRE2_TILE_QUBITS
+#define SRE2_TILE_QUBITS 11
+#endif
+constexpr int kTileQubits = SRE2_TILE_QUBITS;
+constexpr int kLowQubits = 3;  // always in the tile: 128 contiguous bytes
+constexpr int kPassGates = 14;
+struct GatePass {
+    int ngates = 0, tb = 0;
+    uint32_t mask = 0;              // qubits of the tile
+    uint32_t qubit[kSimMaxN] = {};  // tile bits' qubits ascending, then the others
+    uint32_t pair[kPassGates] = {}; // tile bits a < b of each gate: a + 256 b
+    double2 u[kPassGates][16];      // row-major U[i][j], index bit(a) + 2 bit(b)
 };
+static_assert(sizeof(GatePass) <= 4000, "kernel arguments");
 
-__global__ void k_product(double2* __restrict__ psi, int N, const ProductArgs a) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ((int64_t)1 << N)) return;
+// Product over the qubits [lo, hi) of the factors that the bits of k select
+// (f[2 i] for bit i clear, f[2 i + 1] for set).
+__device__ __forceinline__ double2 product_of(const double2* f, uint32_t k, int lo, int hi) {
     double re = 1.0, im = 0.0;
-    for (int i = 0; i < N; ++i) {
-        if ((k >> i) & 1) {
-            const double r = re * a.c1r[i] - im * a.c1i[i];
-            im = re * a.c1i[i] + im * a.c1r[i];
-            re = r;
-        } else {
-            re *= a.c0[i];
-            im *= a.c0[i];
-        }
+    for (int i = lo; i < hi; ++i) {
+        const double2 c = f[2 * i + ((k >> i) & 1)];
+        const double r = re * c.x - im * c.y;
+        im = re * c.y + im * c.x;
+        re = r;
     }
-    psi[k] = make_double2(re, im);
+    return make_double2(re, im);
 }
 
-// One thread per group of four amplitudes that differ in bits q0, q1.
-__global__ void k_gate2(double2* __restrict__ psi, int N, int q0, int q1, const Gate g) {
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= ((int64_t)1 << (N - 2))) return;
-    const int lo = q0 < q1 ? q0 : q1, hi = q0 < q1 ? q1 : q0;
-    // insert zero bits at lo, then hi
-    uint64_t b = (uint64_t)m;
-    b = ((b >> lo) << (lo + 1)) | (b & ((1ull << lo) - 1));
-    b = ((b >> hi) << (hi + 1)) | (b & ((1ull << hi) - 1));
-    uint64_t idx[4];
+// A workgroup writes up to four runs of 256 amplitudes: the product over the low
+// eight qubits once per thread, that over the others once per run, one complex
+// product per amplitude (N factors per amplitude took 18 us at N = 20; 13 now,
+// bound by the 16 MiB it writes).
+constexpr int kProductLow = 8, kProductRunBits = 2, kProductRuns = 1 << kProductRunBits;
+__global__ __launch_bounds__(1 << kProductLow) void k_product(double2* __restrict__ psi, int N,
+                                                              const ProductArgs a) {
+    __shared__ double2 f[2 * kSimMaxN], high[kProductRuns];
+    const int nl = N < kProductLow ? N : kProductLow;
+    const uint32_t first = blockIdx.x * kProductRuns, runs = 1u << (N - nl);
+    const uint32_t tid = threadIdx.x;
+    // the factors at once: read one by one they cost a memory latency each
+    if (tid < 2 * kSimMaxN) f[tid] = a.f[tid];
+    __syncthreads();
+    if (tid < kProductRuns) high[tid] = product_of(f, (first + tid) << kProductLow, nl, N);
+    const double2 low = product_of(f, tid, 0, nl);
+    __syncthreads();
+    if (tid >= 1u << nl) return;
+#pragma unroll
+    for (uint32_t r = 0; r < kProductRuns; ++r) {
+        if (first + r >= runs) break;
+        const double2 h = high[r];
+        psi[((first + r) << kProductLow) + tid] =
+            make_double2(h.x * low.x - h.y * low.y, h.x * low.y + h.y * low.x);
+    }
+}
+
+// LDS slot of tile element e: the low four bits XORed with the higher ones, so
+// that the four-amplitude groups of any pair of tile bits spread over the banks.
+__device__ __forceinline__ uint32_t tile_slot(uint32_t e) {
+    return e ^ ((e >> 4) & 15u) ^ ((e >> 8) & 15u);
+}
+
+// Applies the gates of one pass in order, each thread one group of four
+// amplitudes per gate, through LDS.  What bounds it is the pass over memory
+// (N = 20: 16 MiB read and written) and, per gate, 62 FP64 operations and 128
+// bytes of LDS traffic per group.  Four waves per SIMD hide the LDS and
+// argument loads; the loop body is small on purpose: a variant that held 16
+// amplitudes in registers and unrolled each pair of register bits took
+// 1.7 us per gate (its code ran once or twice per launch, from a cold
+// instruction cache) against 1.1 us.  (One kernel per gate: 7.2 us each.)
+__global__ __launch_bounds__(1 << (kTileQubits - 2)) void k_gates(double2* __restrict__ psi, int N,
+                                                                  const GatePass ps) {
+    constexpr int TBITS = kTileQubits - 2;
+    constexpr uint32_t T = 1u << TBITS;
+    __shared__ double2 t[1 << kTileQubits];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t size = 1u << ps.tb;
+    uint32_t at = 0;
+    for (int b = 0; b < N - ps.tb; ++b) at |= ((blockIdx.x >> b) & 1u) << ps.qubit[ps.tb + b];
+#pragma unroll
+    for (int b = 0; b < TBITS; ++b)
+        if (b < ps.tb) at |= ((tid >> b) & 1u) << ps.qubit[b];
+    // the tile bits above the thread's
+    const uint32_t u0 = TBITS < ps.tb ? 1u << ps.qubit[TBITS] : 0u;
+    const uint32_t u1 = TBITS + 1 < ps.tb ? 1u << ps.qubit[TBITS + 1] : 0u;
     double2 a[4];
+    // all loads in flight before the first LDS write; elements above a smaller
+    // tile repeat its own addresses and land in slots that nothing stores
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        idx[j] = b | ((uint64_t)(j & 1) << q0) | ((uint64_t)(j >> 1) << q1);
-        a[j] = psi[idx[j]];
-    }
+    for (int i = 0; i < 4; ++i) a[i] = psi[at | (i & 1 ? u0 : 0u) | (i & 2 ? u1 : 0u)];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        double re = 0.0, im = 0.0;
+    for (int i = 0; i < 4; ++i) t[tile_slot(i * T + tid)] = a[i];
+    for (int g = 0; g < ps.ngates; ++g) {
+        const uint32_t lo = ps.pair[g] & 255u, hi = ps.pair[g] >> 8;
+        // insert zero bits at lo, then hi (the threads above a smaller tile
+        // work on slots of their own); slots of disjoint bits combine by XOR
+        uint32_t m = ((tid >> lo) << (lo + 1)) | (tid & ((1u << lo) - 1u));
+        m = ((m >> hi) << (hi + 1)) | (m & ((1u << hi) - 1u));
+        const uint32_t s0 = tile_slot(m), sl = tile_slot(1u << lo), sh = tile_slot(1u << hi);
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            re += g.re[4 * i + j] * a[j].x - g.im[4 * i + j] * a[j].y;
-            im += g.re[4 * i + j] * a[j].y + g.im[4 * i + j] * a[j].x;
+        for (int j = 0; j < 4; ++j) a[j] = t[s0 ^ (j & 1 ? sl : 0u) ^ (j & 2 ? sh : 0u)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double re = 0.0, im = 0.0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double2 c = ps.u[g][4 * i + j];
+                re = __builtin_fma(c.x, a[j].x, re);
+                im = __builtin_fma(c.x, a[j].y, im);
+                re = __builtin_fma(-c.y, a[j].y, re);
+                im = __builtin_fma(c.y, a[j].x, im);
+            }
+            t[s0 ^ (i & 1 ? sl : 0u) ^ (i & 2 ? sh : 0u)] = make_double2(re, im);
         }
-        psi[idx[i]] = make_double2(re, im);
     }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (i * T + tid < size)
+            psi[at | (i & 1 ? u0 : 0u) | (i & 2 ? u1 : 0u)] = t[tile_slot(i * T + tid)];
 }
 
 // acc = c * v
@@ -158,6 +234,10 @@ std::vector<double> bessel_j(double x, int M) {
     return out;
 }
 
+unsigned product_blocks(int N) {
+    const int run_bits = kProductLow + kProductRunBits;
+    return N > run_bits ? 1u << (N - run_bits) : 1u;
+}
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
@@ -231,16 +311,55 @@ int tfim_step(sre2_sim* s, double J, double hx, double hz, double dt) {
     return launched();
 }
 
+// Gates in passes of k_gates.  A pass takes, in list order, every gate whose
+// qubits fit its tile and that shares no qubit with a gate left for a later
+// pass, so gates only move past gates they commute with.  It looks at most
+// kLookAhead gates ahead, which bounds the planning per pass.
+constexpr int kLookAhead = 256;
 int apply_gates(sre2_sim* s, const double* gates, const int* pairs, int count) {
-    const int64_t groups = int64_t(1) << (s->N - 2);
-    for (int g = 0; g < count; ++g) {
-        Gate G;
-        for (int e = 0; e < 16; ++e) {
-            G.re[e] = gates[32 * g + 2 * e];
-            G.im[e] = gates[32 * g + 2 * e + 1];
+    const int tb = s->N < kTileQubits ? s->N : kTileQubits;
+    int todo[kLookAhead];  // the next gates in order; `next` follows them
+    int ntodo = 0, next = 0;
+    for (;;) {
+        while (ntodo < kLookAhead && next < count) todo[ntodo++] = next++;
+        if (ntodo == 0) break;
+        GatePass ps;
+        ps.tb = tb;
+        ps.mask = (1u << (s->N < kLowQubits ? s->N : kLowQubits)) - 1u;
+        int taken[kPassGates], left = 0;
+        uint32_t blocked = 0;
+        for (int i = 0; i < ntodo; ++i) {
+            const int g = todo[i];
+            const uint32_t qs = (1u << pairs[2 * g]) | (1u << pairs[2 * g + 1]);
+            if (ps.ngates == kPassGates || (qs & blocked) ||
+                __builtin_popcount(ps.mask | qs) > tb) {
+                blocked |= qs;
+                todo[left++] = g;
+            } else {
+                ps.mask |= qs;
+                taken[ps.ngates++] = g;
+            }
         }
-        hipLaunchKernelGGL(k_gate2, dim3(blocks_for(groups)), dim3(256), 0, s->st, s->psi, s->N,
-                           pairs[2 * g], pairs[2 * g + 1], G);
+        ntodo = left;
+        for (int q = 0; __builtin_popcount(ps.mask) < tb; ++q) ps.mask |= 1u << q;
+        for (int q = 0, b = 0, o = tb; q < s->N; ++q)
+            ps.qubit[(ps.mask >> q) & 1u ? b++ : o++] = (uint32_t)q;
+        for (int i = 0; i < ps.ngates; ++i) {
+            const int* pr = pairs + 2 * taken[i];
+            const uint32_t p0 = __builtin_popcount(ps.mask & ((1u << pr[0]) - 1u));
+            const uint32_t p1 = __builtin_popcount(ps.mask & ((1u << pr[1]) - 1u));
+            const bool swap = p0 > p1;
+            ps.pair[i] = swap ? p1 + 256 * p0 : p0 + 256 * p1;
+            const double* U = gates + 32 * (size_t)taken[i];
+            for (int e = 0; e < 16; ++e) {
+                // with the pair swapped the bits of both indices swap too
+                const int r = e >> 2, c = e & 3;
+                const int f = swap ? 4 * (r >> 1 | (r & 1) << 1) + (c >> 1 | (c & 1) << 1) : e;
+                ps.u[i][e] = make_double2(U[2 * f], U[2 * f + 1]);
+            }
+        }
+        hipLaunchKernelGGL(k_gates, dim3(1u << (s->N - tb)), dim3(1 << (kTileQubits - 2)), 0,
+                           s->st, s->psi, s->N, ps);
     }
     return launched();
 }
@@ -340,9 +459,9 @@ int sre2_sim_create(sre2_sim** out, int hip_device, int N) {
     }
     // start in |0...0> (the product state with every theta_i = 0)
     ProductArgs a{};
-    for (int i = 0; i < N; ++i) a.c0[i] = 1.0;
-    hipLaunchKernelGGL(k_product, dim3(blocks_for(int64_t(1) << N)), dim3(256), 0, s->st, s->psi,
-                       N, a);
+    for (int i = 0; i < N; ++i) a.f[2 * i] = make_double2(1.0, 0.0);
+    hipLaunchKernelGGL(k_product, dim3(product_blocks(N)), dim3(1 << kProductLow), 0, s->st,
+                       s->psi, N, a);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s->st) != hipSuccess) {
         sre2_sim_destroy(s);
         return SRE2_EHIP;
@@ -373,12 +492,11 @@ int sre2_sim_product_state(sre2_sim* s, const double* theta, const double* phi) 
     ProductArgs a{};
     for (int i = 0; i < s->N; ++i) {
         const double c = std::cos(0.5 * theta[i]), sn = std::sin(0.5 * theta[i]);
-        a.c0[i] = c;
-        a.c1r[i] = std::cos(phi[i]) * sn;
-        a.c1i[i] = std::sin(phi[i]) * sn;
+        a.f[2 * i] = make_double2(c, 0.0);
+        a.f[2 * i + 1] = make_double2(std::cos(phi[i]) * sn, std::sin(phi[i]) * sn);
     }
-    const int64_t n = int64_t(1) << s->N;
-    hipLaunchKernelGGL(k_product, dim3(blocks_for(n)), dim3(256), 0, s->st, s->psi, s->N, a);
+    hipLaunchKernelGGL(k_product, dim3(product_blocks(s->N)), dim3(1 << kProductLow), 0, s->st,
+                       s->psi, s->N, a);
     return launched();
 }
 
