@@ -25,6 +25,7 @@
 #include <cmath>
 #include <new>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "../../include/sre2.h"
@@ -168,49 +169,152 @@ __global__ __launch_bounds__(1 << (kTileQubits - 2)) void k_gates(double2* __res
             psi[at | (i & 1 ? u0 : 0u) | (i & 2 ? u1 : 0u)] = t[tile_slot(i * T + tid)];
 }
 
-// acc = c * v
-__global__ void k_scale_into(const double2* __restrict__ v, double2* __restrict__ acc, int64_t n,
-                             double cr, double ci) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const double2 x = v[k];
-    acc[k] = make_double2(cr * x.x - ci * x.y, cr * x.y + ci * x.x);
+// H of the TFIM chain, scaled by 1/a: its diagonal part at basis state k
+// (Ising and longitudinal-field energies, Z|0> = |0>); the field along x adds
+// -hx times the N single-bit flips.
+struct Tfim {
+    double J, hx, hz, inv_a;
+};
+__device__ __forceinline__ double tfim_diag(const Tfim& h, int N, uint32_t k) {
+    const int bonds_flipped = (int)__popc((k ^ (k >> 1)) & ((1u << (N - 1)) - 1u));
+    const int ones = (int)__popc(k & ((1u << N) - 1u));
+    return -h.J * (double)((N - 1) - 2 * bonds_flipped) - h.hz * (double)(N - 2 * ones);
+}
+// T_{k+1} from h = H T_k and T_{k-1} (first: T_1 = h T_0).
+__device__ __forceinline__ double2 cheb_next(double2 h, double2 older, bool first) {
+    return first ? h : make_double2(2.0 * h.x - older.x, 2.0 * h.y - older.y);
+}
+// s + m (-i)^k t, m carrying the sign of the time step.
+__device__ __forceinline__ double2 cheb_add(double2 s, double m, int k, double2 t) {
+    const double g = k & 2 ? -m : m;
+    if (k & 1)
+        return make_double2(s.x + g * t.y, s.y - g * t.x);
+    return make_double2(s.x + g * t.x, s.y + g * t.y);
 }
 
-// One Chebyshev term: h = (H / a) cur; next = h (first) or 2 h - prev,
-// written over prev; acc += c * next.  H is applied as its diagonal
-// (Ising and longitudinal-field energies of basis state k, Z|0> = |0>) plus
-// -hx times the N single-bit flips.
-__global__ void k_cheb(const double2* __restrict__ cur, double2* __restrict__ prev,
-                       double2* __restrict__ acc, int N, double J, double hx, double hz,
-                       double inv_a, double cr, double ci, int first) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ((int64_t)1 << N)) return;
-    const uint64_t u = (uint64_t)k;
-    const int bonds_flipped = __popcll((u ^ (u >> 1)) & ((1ull << (N - 1)) - 1));
-    const int ones = __popcll(u);
-    const double diag = -J * (double)((N - 1) - 2 * bonds_flipped) - hz * (double)(N - 2 * ones);
-    const double2 c = cur[k];
-    double hr = diag * c.x, hi = diag * c.y;
-    for (int i = 0; i < N; ++i) {
-        const double2 f = cur[u ^ (1ull << i)];
-        hr -= hx * f.x;
-        hi -= hx * f.y;
+// One Chebyshev term, N = 8 + AB + NH: writes T_k over T_{k-2} and adds its
+// share m (-i)^k T_k to acc (first: k = 1, acc starts as m0 T_0).  A workgroup
+// holds 2^AB runs of 256 amplitudes: the flips of the low eight bits come from
+// LDS, those of the next AB bits from the thread's own registers, the NH high
+// ones from memory, all loads in flight at once (N = 16: one after the other
+// they took 4.8 us per term).
+template <int NH, int AB>
+__global__ __launch_bounds__(256) void k_cheb(const double2* __restrict__ cur,
+                                              double2* __restrict__ older,
+                                              double2* __restrict__ acc, const Tfim h, double m0,
+                                              double m, int k) {
+    constexpr int LB = 8 + AB, N = LB + NH, A = 1 << AB;
+    __shared__ double2 run[A][256];
+    const uint32_t t = threadIdx.x, base = (blockIdx.x << LB) + t;
+    const bool first = k == 1;
+    double2 c[A], f[A], o[A], s[A];
+#pragma unroll
+    for (int i = 0; i < A; ++i) c[i] = cur[base + 256 * i];
+    double2 far[A][NH];
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+#pragma unroll
+        for (int b = 0; b < NH; ++b) far[i][b] = cur[(base ^ (1u << (LB + b))) + 256 * i];
+        o[i] = first ? make_double2(0.0, 0.0) : older[base + 256 * i];
+        s[i] = first ? make_double2(0.0, 0.0) : acc[base + 256 * i];
     }
-    hr *= inv_a;
-    hi *= inv_a;
-    double2 nx;
-    if (first) {
-        nx = make_double2(hr, hi);
-    } else {
-        const double2 p = prev[k];
-        nx = make_double2(2.0 * hr - p.x, 2.0 * hi - p.y);
+#pragma unroll
+    for (int i = 0; i < A; ++i) run[i][t] = c[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+        f[i] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const double2 v = run[i][t ^ (1u << b)];
+            f[i].x += v.x;
+            f[i].y += v.y;
+        }
+#pragma unroll
+        for (int b = 0; b < AB; ++b) {
+            f[i].x += c[i ^ (1 << b)].x;
+            f[i].y += c[i ^ (1 << b)].y;
+        }
+#pragma unroll
+        for (int b = 0; b < NH; ++b) {
+            f[i].x += far[i][b].x;
+            f[i].y += far[i][b].y;
+        }
+        const uint32_t q = base + 256 * i;
+        const double d = tfim_diag(h, N, q);
+        const double2 hc = make_double2((d * c[i].x - h.hx * f[i].x) * h.inv_a,
+                                        (d * c[i].y - h.hx * f[i].y) * h.inv_a);
+        const double2 nx = cheb_next(hc, o[i], first);
+        older[q] = nx;
+        if (first) s[i] = make_double2(m0 * c[i].x, m0 * c[i].y);
+        acc[q] = cheb_add(s[i], m, k, nx);
     }
-    prev[k] = nx;
-    double2 s = acc[k];
-    s.x += cr * nx.x - ci * nx.y;
-    s.y += cr * nx.y + ci * nx.x;
-    acc[k] = s;
+}
+
+// Up to kSmallTerms terms of a state of N <= kSmallMaxN qubits in one launch:
+// one workgroup holds T_k, T_{k-1} and the sum in registers and exchanges T_k
+// through LDS (two buffers, one barrier per term).  A launch per term is
+// bound by the launch (5 us each at N = 10).
+constexpr int kSmallMaxN = 11, kSmallTerms = 128;
+struct ChebCoef {
+    double m[kSmallTerms + 1];
+};
+__global__ __launch_bounds__(1024) void k_cheb_small(double2* __restrict__ newer,
+                                                     double2* __restrict__ older,
+                                                     double2* __restrict__ acc, int N,
+                                                     const Tfim h, int k0, int count,
+                                                     const ChebCoef m) {
+    constexpr int A = 1 << (kSmallMaxN - 10);
+    __shared__ double2 buf[2][1 << kSmallMaxN];
+    const uint32_t size = 1u << N, t = threadIdx.x;
+    double2 c[A], o[A], s[A];
+    double d[A];
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+        const uint32_t q = t + 1024 * i;
+        c[i] = o[i] = s[i] = make_double2(0.0, 0.0);
+        if (q < size) {
+            c[i] = newer[q];
+            if (k0 > 1) {
+                o[i] = older[q];
+                s[i] = acc[q];
+            } else {
+                s[i] = make_double2(m.m[0] * c[i].x, m.m[0] * c[i].y);
+            }
+        }
+        d[i] = tfim_diag(h, N, q);
+    }
+    for (int j = 0; j < count; ++j) {
+        double2* __restrict__ b = buf[j & 1];
+#pragma unroll
+        for (int i = 0; i < A; ++i) b[t + 1024 * i] = c[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < A; ++i) {
+            const uint32_t q = t + 1024 * i;
+            double2 f = make_double2(0.0, 0.0);
+            for (int g = 0; g < N; ++g) {
+                const double2 v = b[q ^ (1u << g)];
+                f.x += v.x;
+                f.y += v.y;
+            }
+            const double2 hc = make_double2((d[i] * c[i].x - h.hx * f.x) * h.inv_a,
+                                            (d[i] * c[i].y - h.hx * f.y) * h.inv_a);
+            const double2 nx = cheb_next(hc, o[i], k0 + j == 1);
+            o[i] = c[i];
+            c[i] = nx;
+            s[i] = cheb_add(s[i], m.m[j + 1], k0 + j, nx);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+        const uint32_t q = t + 1024 * i;
+        if (q < size) {
+            newer[q] = c[i];
+            older[q] = o[i];
+            acc[q] = s[i];
+        }
+    }
 }
 
 // Bessel functions J_0..J_M(x), x > 0, by Miller's backward recurrence
@@ -269,40 +373,61 @@ struct Guard {
 
 int launched() { return hipGetLastError() == hipSuccess ? SRE2_OK : SRE2_EHIP; }
 
+// From kChebRuns qubits on a workgroup takes four runs: the flips of ten bits
+// stay on chip, at 256 workgroups or more.
+constexpr int kChebRuns = 18;
+template <int N>
+void launch_cheb(sre2_sim* s, const double2* cur, double2* older, const Tfim& h, double m0,
+                 double m, int k) {
+    constexpr int AB = N >= kChebRuns ? 2 : 0;
+    hipLaunchKernelGGL((k_cheb<N - 8 - AB, AB>), dim3(1u << (N - 8 - AB)), dim3(256), 0, s->st,
+                       cur, older, s->acc, h, m0, m, k);
+}
+template <int... Ns>
+void dispatch_cheb(sre2_sim* s, const double2* cur, double2* older, const Tfim& h, double m0,
+                   double m, int k, std::integer_sequence<int, Ns...>) {
+    ((s->N == Ns + kSmallMaxN + 1
+          ? launch_cheb<Ns + kSmallMaxN + 1>(s, cur, older, h, m0, m, k)
+          : void()),
+     ...);
+}
+
 int tfim_step(sre2_sim* s, double J, double hx, double hz, double dt) {
     const int N = s->N;
-    const int64_t n = int64_t(1) << N;
-    // ||H|| <= |J| (N - 1) + (|hx| + |hz|) N
-    const double a = std::fabs(J) * (N - 1) + (std::fabs(hx) + std::fabs(hz)) * N;
+    // ||H|| <= |J| (N - 1) + N |(hx, hz)|: a site's field has the norm of the
+    // vector (the sum |hx| + |hz| takes 40 terms instead of 35 at N = 16 and
+    // the quench example's parameters)
+    const double a = std::fabs(J) * (N - 1) + std::hypot(hx, hz) * N;
     if (!(a > 0.0) || dt == 0.0) return SRE2_OK;  // H = 0 or no time: identity
     const double x = a * std::fabs(dt);
     int M = (int)(x + 30.0 + 5.0 * std::cbrt(x));
     const std::vector<double> jb = bessel_j(x, M);
     int K = M;
     while (K > (int)x + 1 && std::fabs(jb[K]) < 1e-17) --K;
-    // coefficient of T_k: (2 - [k = 0]) (-i sgn(dt))^k J_k(x)
-    auto coef = [&](int k, double* cr, double* ci) {
-        const double m = (k == 0 ? 1.0 : 2.0) * jb[k];
-        const int r = k & 3;
-        const double sg = dt > 0 ? 1.0 : -1.0;
-        // (-i sg)^k: r = 0 -> 1, 1 -> -i sg, 2 -> -1, 3 -> i sg
-        *cr = r == 0 ? m : (r == 2 ? -m : 0.0);
-        *ci = r == 1 ? -sg * m : (r == 3 ? sg * m : 0.0);
+    // share of T_k: (2 - [k = 0]) (-i sgn(dt))^k J_k(x) = m_k (-i)^k
+    const auto share = [&](int k) {
+        return (k == 0 ? 1.0 : 2.0) * (dt < 0 && (k & 1) ? -jb[k] : jb[k]);
     };
-    const unsigned nb = blocks_for(n);
-    double cr, ci;
-    coef(0, &cr, &ci);
-    hipLaunchKernelGGL(k_scale_into, dim3(nb), dim3(256), 0, s->st, s->psi, s->acc, n, cr, ci);
-    // buffers: psi holds T_0, wb receives T_1; then the newer overwrites the older
-    double2* older = s->wb;  // T_{k-1} slot that receives T_{k+1}
-    double2* newer = s->psi;
-    for (int k = 1; k <= K; ++k) {
-        coef(k, &cr, &ci);
-        hipLaunchKernelGGL(k_cheb, dim3(nb), dim3(256), 0, s->st, newer, older, s->acc, N, J, hx,
-                           hz, 1.0 / a, cr, ci, k == 1 ? 1 : 0);
-        double2* t = older;
-        older = newer;
-        newer = t;
+    const Tfim h{J, hx, hz, 1.0 / a};
+    // psi holds T_0, wb receives T_1; then the newer overwrites the older
+    double2 *older = s->wb, *newer = s->psi;
+    if (N <= kSmallMaxN) {
+        for (int k = 1; k <= K; k += kSmallTerms) {
+            const int n = K - k + 1 < kSmallTerms ? K - k + 1 : kSmallTerms;
+            ChebCoef m;
+            m.m[0] = share(0);
+            for (int j = 0; j < n; ++j) m.m[j + 1] = share(k + j);
+            hipLaunchKernelGGL(k_cheb_small, dim3(1), dim3(1024), 0, s->st, newer, older, s->acc,
+                               N, h, k, n, m);
+        }
+    } else {
+        for (int k = 1; k <= K; ++k) {
+            dispatch_cheb(s, newer, older, h, share(0), share(k), k,
+                          std::make_integer_sequence<int, kSimMaxN - kSmallMaxN>{});
+            double2* t = older;
+            older = newer;
+            newer = t;
+        }
     }
     // the sum is the new state; keep the buffers distinct
     double2* t = s->psi;
