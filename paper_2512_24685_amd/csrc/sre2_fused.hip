@@ -33,10 +33,7 @@ __global__ __launch_bounds__(64) void k_tiny(const typename CT<Real>::T* __restr
 #pragma unroll
             for (int k = 0; k < D; ++k) v[k] = cmul_conj_a(psi[k ^ x], psi[k]);
             butterflies<N, (1u << N) - 1u, (1u << N) - 1u>(v);
-            double s = 0.0;
-#pragma unroll
-            for (int z = 0; z < D; ++z) s += gen_terms<Real, false>(v[z], sp, lnorm2, lh);
-            S_out[idx] = s;
+            S_out[idx] = gen_sum<Real, GEN_PLAIN, true>(v, sp, lnorm2, lh);
         }
         hist_flush(lh, sp);
         return;
@@ -193,11 +190,8 @@ void k_fused(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int6
             // registers lie inside the transform bits); empty slots of the
             // last tile hold zeros that must not enter the histogram
             const int64_t slot = thread_base<rl.lperm, rl.wave>() >> NT;
-            if (tile * SPT + slot < x_count) {
-#pragma unroll
-                for (int i = 0; i < (1 << RB); ++i)
-                    s += gen_terms<Real, HERM>(v[i], sp, lnorm2, lh);
-            }
+            if (tile * SPT + slot < x_count)
+                s = gen_sum<Real, HERM ? GEN_HERM : GEN_PLAIN, true>(v, sp, lnorm2, lh);
         } else {
 #pragma unroll
             for (int i = 0; i < (1 << RB); ++i) s += HERM ? abs4h(v[i]) : abs4(v[i]);

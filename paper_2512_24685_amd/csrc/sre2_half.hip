@@ -155,24 +155,33 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin,
     const auto rs = buf_rsrc(psi, (uint32_t)sizeof(C) << N);
     const uint32_t x = (uint32_t)x_begin + blockIdx.x;
     const bool zero = x == 0;
-    // element e -> k = insert0(e, hb), and the pair k ^ xl; insert0 and the XOR
-    // act on disjoint bits of the thread's and the register's part of e, so
-    // the register's part of an address is uniform (a scalar offset)
-    const uint32_t xl = zero ? 1u << HB0 : x;
-    const uint32_t hb = 31u - __clz(xl);
-    const uint32_t R = insert0(r0.reg, hb);
-    const uint32_t kb = insert0(thread_base<r0.lperm, r0.wave>(), hb);
-    const uint32_t vb = kb ^ (xl & ~R), xr = xl & R;
+    const uint32_t base = thread_base<r0.lperm, r0.wave>();
     C v[NE];
     if (zero) {
-#pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const uint32_t kr = insert0(pdep((uint32_t)i, r0.reg), hb);
-            const C a = load_at<C>(rs, vb, kr ^ xr), c = load_at<C>(rs, kb, kr);
-            v[i].x = cmul_conj_a(c, c).x;
-            v[i].y = cmul_conj_a(a, a).x;
-        }
+        // a rolled loop through the thread's own LDS slots, so that one
+        // workgroup's case does not cost the others registers
+        static_assert(r0.reg == top_bits(bits_range(0, NT), RB), "element bits of a register");
+        const auto squares = [&](uint32_t bit) {
+#pragma unroll 1
+            for (uint32_t i = 0; i < NE; ++i) {
+                const uint32_t e = base | (i << (NT - RB));
+                const C c = load_at<C>(rs, insert0(e, HB0) | bit, 0);
+                lds[pad16<5>(e)] = cmul_conj_a(c, c).x;
+            }
+        };
+        squares(0u);
+        lds_part<false, 0, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
+        squares(1u << HB0);
+        lds_part<false, 1, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
     } else {
+        // element e -> k = insert0(e, hb), and the partner k ^ x; insert0 and
+        // the XOR act on disjoint bits of the thread's and the register's part
+        // of e, so the register's part of an address is uniform (a scalar
+        // offset)
+        const uint32_t hb = 31u - __clz(x);
+        const uint32_t R = insert0(r0.reg, hb);
+        const uint32_t kb = insert0(base, hb);
+        const uint32_t vb = kb ^ (x & ~R), xr = x & R;
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             const uint32_t kr = insert0(pdep((uint32_t)i, r0.reg), hb);
@@ -182,27 +191,25 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin,
     butterflies<RB, r0.reg, r0.bfly>(v);
     HR::run(lds, v);
     double acc = 0.0;
-    if (zero) {
+    if (zero) {  // the last stage, across the two halves
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             const Real a = v[i].x + v[i].y, c = v[i].x - v[i].y;
-            if constexpr (GEN) {
-                acc += gen_term<Real>(a * a, sp, Real(0), nullptr) +
-                       gen_term<Real>(c * c, sp, Real(0), nullptr);
-            } else {
-                const double da = (double)(a * a), dc = (double)(c * c);
-                acc += da * da + dc * dc;
-            }
+            v[i].x = a;
+            v[i].y = c;
         }
+        if constexpr (GEN) {
+            acc = gen_sum<Real, GEN_SQUARES, false>(v, sp, Real(0), nullptr);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NE; ++i) acc += abs4h(v[i]);
+        }
+    } else if constexpr (GEN) {
+        acc = gen_sum<Real, GEN_HERM, false>(v, sp, Real(0), nullptr);
     } else {
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            if constexpr (GEN)
-                acc += gen_terms<Real, true>(v[i], sp, Real(0), nullptr);
-            else
-                acc += abs4h(v[i]);
-        }
-        if constexpr (!GEN) acc *= 16.0;
+        for (int i = 0; i < NE; ++i) acc += abs4h(v[i]);
+        acc *= 16.0;
     }
     acc = wave_sum(acc);
     if constexpr (NW == 1) {

@@ -60,6 +60,7 @@ constexpr int kMaxBins = 64;
 struct Spec {
     int kind = kRedQuartic;
     int nbins = 0;
+    int ipow = 0;  // kRedPow: alpha where it is 3 or 4 (taken as products), else 0
     double alpha = 2.0;
     const double* nrm = nullptr;         // device: n = sum |psi|^2 (histogram)
     unsigned long long* hist = nullptr;  // device: nbins counters (histogram)

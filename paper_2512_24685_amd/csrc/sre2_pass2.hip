@@ -100,11 +100,11 @@ void k_pass2(const typename CT<Real>::T* __restrict__ scratch, int NS, int P,
     // column transform of one tile and its terms, tiles in ascending order
     const auto consume = [&](C (&v)[1 << RB]) {
         run_transform<Real, TB, RB, PK>(lds, v);
+        if constexpr (GEN) {
+            acc += gen_sum<Real, HALF == HALF_SLAB ? GEN_HERM : GEN_PLAIN, true>(v, sp, lnorm2, lh);
+        } else {
 #pragma unroll
-        for (int i = 0; i < (1 << RB); ++i) {
-            if constexpr (GEN)
-                acc += gen_terms<Real, HALF == HALF_SLAB>(v[i], sp, lnorm2, lh);
-            else
+            for (int i = 0; i < (1 << RB); ++i)
                 acc += HALF == HALF_SLAB ? abs4h(v[i]) : abs4(v[i]);
         }
     };
