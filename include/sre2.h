@@ -144,9 +144,9 @@ int sre2_set_scratch_limit(sre2_ctx* ctx, size_t bytes);
  * way, bit for bit; in the split forms (whose H_16 products on the matrix
  * cores sum in an order the permutation does not preserve) results differ
  * from the full slab's by rounding only, within the same error bound.  The
- * general index (sre2_sre) takes the row pairs too; the spectrum
- * (sre2_pauli_spectrum) always takes the full slab.  Sizes evaluated on chip
- * have no slab.  Errors: SRE2_EINVAL (ctx == NULL). */
+ * general index (sre2_sre) takes the row pairs too, and the spectrum
+ * (sre2_pauli_spectrum) in FP64 and, up to N = 17, in FP32 (its counts are
+ * those of the full slab).  Sizes evaluated on chip have no slab.  Errors: SRE2_EINVAL (ctx == NULL). */
 int sre2_set_row_pairs(sre2_ctx* ctx, int enable);
 
 /* First shift x of an N-qubit evaluation that takes a half slab in the

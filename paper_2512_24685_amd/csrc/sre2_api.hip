@@ -98,8 +98,9 @@ int row_bits(int form, int NS) {
 int herm_min(int form) { return is_f64(form) ? herm_min_n<double>() : herm_min_n<float>(); }
 // The half transforms take this evaluation (spec: its reduction, null for M2).
 bool half_path(int N, int form, const Spec* spec) {
-    return !is_split(form) && !(spec && spec->kind == kRedHist) &&
-           (is_f64(form) ? half_takes<double>(N) : half_takes<float>(N));
+    const bool hist = spec && spec->kind == kRedHist;
+    return !is_split(form) &&
+           (is_f64(form) ? half_takes<double>(N, hist) : half_takes<float>(N, hist));
 }
 int half_first(int N, int form) {
     return is_f64(form) ? half_first_shift<double>(N) : half_first_shift<float>(N);
@@ -150,12 +151,16 @@ Chunking chunking(int N, int form, int slab, int64_t x_count, size_t limit) {
 
 // Slab kind of the shifts of a two-pass evaluation that need not take the
 // full slab (spec: its reduction, null for M2; pairs: row pairs allowed).  The
-// histogram keeps the plain transform's stage order, as its counts depend on
-// every rounding; so do the reductions that have no comparison kernel when
-// row pairs are off.
-int high_slab(int form, bool pairs, const Spec* spec) {
+// FP32 histogram's counts depend on every rounding, so it takes the row pairs
+// only where pass 2 is one round (row bits upwards, so that the top set bit of
+// x >> L comes after every other set bit, and the values keep every bit of
+// the plain transform); the reductions that have no comparison kernel keep
+// the full slab when row pairs are off.
+int high_slab(int N, int form, bool pairs, const Spec* spec) {
     if (is_herm(form)) return kSlabHerm;
-    if (spec && spec->kind == kRedHist) return kSlabFull;
+    if (spec && spec->kind == kRedHist && !is_f64(form) &&
+        N - slab_rows(form, N, kSlabFull) > pass2_round_bits<float>())
+        return kSlabFull;
     if (pairs) return kSlabPairs;
     return spec || is_split(form) ? kSlabFull : kSlabBoth;
 }
@@ -327,7 +332,7 @@ int64_t slab_need(int N, int form, int high, int64_t x0, int64_t xc, size_t limi
 int ctx_two_pass_ws(sre2_ctx* ctx, int N, int form, int64_t x0, int64_t xc, const Spec* spec,
                     Workspace* ws) {
     ws->pairs = ctx->row_pairs;
-    const int high = high_slab(form, ws->pairs, spec);
+    const int high = high_slab(N, form, ws->pairs, spec);
     xc = two_pass_shifts(N, form, half_path(N, form, spec), x0, xc);
     if (xc == 0) return SRE2_OK;
     size_t limit = ctx->scratch_limit, need = 0, need_part = 0;
@@ -364,9 +369,10 @@ int shift_sums(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int
         }
         if (xc == two) return SRE2_OK;
         Timed tm(tctx, st, SRE2_KIND_SHIFT);
-        return hip_status(f64 ? launch_shift_kernel<double>(work, N, true, 0, x0 + two, xc - two,
+        const bool herm = is_herm(form);
+        return hip_status(f64 ? launch_shift_kernel<double>(work, N, herm, 0, x0 + two, xc - two,
                                                             Sx + two, se, Pack{}, spec, st)
-                              : launch_shift_kernel<float>(work, N, true, 0, x0 + two, xc - two,
+                              : launch_shift_kernel<float>(work, N, herm, 0, x0 + two, xc - two,
                                                            Sx + two, se, Pack{}, spec, st));
     }
     const int64_t x1 = x0 + xc;
@@ -394,7 +400,7 @@ int shift_sums(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int
         return SRE2_OK;
     }
     SlabRange rg[2];
-    const int nr = slab_ranges(N, form, high_slab(form, ws.pairs, spec), x0, xc, rg);
+    const int nr = slab_ranges(N, form, high_slab(N, form, ws.pairs, spec), x0, xc, rg);
     for (int i = 0; i < nr; ++i) {
         const int rc = two_pass(tctx, ws, work, N, form, rg[i].slab, rg[i].x0, rg[i].xc,
                                 Sx + (rg[i].x0 - x0), se, spec, st);
@@ -532,10 +538,10 @@ int m2_pack(sre2_ctx* ctx, const void* const* psi, int count, int N, int dtype, 
         Timed tm(ctx, st, SRE2_KIND_SHIFT);
         // the half transforms take every shift of a packed size, 0 included
         const int64_t plain_end = herm ? 1 : n;
-        hipError_t e = f64 ? launch_shift_kernel<double>(nullptr, N, half, false, 0,
+        hipError_t e = f64 ? launch_shift_kernel<double>(nullptr, N, false, false, 0,
                                                          half ? n : plain_end, nullptr, nullptr,
                                                          pk, nullptr, st)
-                           : launch_shift_kernel<float>(nullptr, N, half, sp, 0,
+                           : launch_shift_kernel<float>(nullptr, N, false, sp, 0,
                                                         half ? n : plain_end, nullptr, nullptr,
                                                         pk, nullptr, st);
         if (e == hipSuccess && herm && !half)
@@ -581,7 +587,7 @@ int ws_layout(int N, int dtype, int form, bool need_sx, size_t bytes, size_t* ps
     // the largest chunks whose slab and partials fit what is left
     size_t lim = bytes - off, need = 0, need_part = 0;
     for (;;) {
-        const int64_t cs = slab_need(N, form, high_slab(form, true, nullptr), 0, xc, lim, &need, &need_part);
+        const int64_t cs = slab_need(N, form, high_slab(N, form, true, nullptr), 0, xc, lim, &need, &need_part);
         const size_t pb = up(need_part * sizeof(double));
         if (off + pb + need <= bytes) {
             *part_off = off;
@@ -690,7 +696,7 @@ size_t sre2_workspace_bytes(int N, int dtype, int form) {
     if (work_dtype(form) != dtype) b += n * (size_t)elem_bytes(work_dtype(form));
     if (N > fused_max(form)) {
         size_t slab = 0, part = 0;
-        slab_need(N, form, high_slab(form, true, nullptr), 0, (int64_t)n, kDefaultScratchLimit, &slab,
+        slab_need(N, form, high_slab(N, form, true, nullptr), 0, (int64_t)n, kDefaultScratchLimit, &slab,
                   &part);
         b += slab + part * sizeof(double);
     }
@@ -862,7 +868,7 @@ int sre2_chunking(sre2_ctx* ctx, int N, int form, int64_t* shifts_per_chunk, int
     // the chunks of the high shifts x >= 2^L, most of an evaluation
     SlabRange rg[2];
     const int64_t n = int64_t(1) << N;
-    const int nr = slab_ranges(N, form, high_slab(form, ctx->row_pairs, nullptr), 0, n, rg);
+    const int nr = slab_ranges(N, form, high_slab(N, form, ctx->row_pairs, nullptr), 0, n, rg);
     const Chunking ch = chunking(N, form, rg[nr - 1].slab, n, ctx->scratch_limit);
     *shifts_per_chunk = ch.cs;
     *groups = ch.P;
@@ -875,7 +881,7 @@ int64_t sre2_half_slab_first_shift(int N, int form) {
     const int64_t n = int64_t(1) << N;
     if (N <= fused_max(form)) return n;
     SlabRange rg[2];
-    const int nr = slab_ranges(N, form, high_slab(form, true, nullptr), 0, n, rg);
+    const int nr = slab_ranges(N, form, high_slab(N, form, true, nullptr), 0, n, rg);
     return rg[nr - 1].slab == kSlabFull ? n : rg[nr - 1].x0;
 }
 

@@ -51,6 +51,8 @@ __device__ __forceinline__ double abs4h(C w) {
     return __builtin_fma(a, a, b * b);
 }
 
+constexpr int kHistCopies = 16;  // LDS counters per histogram bin
+
 // Histogram bin of one w = |W|^2: lnorm2 = log2(n^2).
 template <typename Real>
 __device__ __forceinline__ int hist_bin(Real w, const Spec& sp, Real lnorm2) {
@@ -64,14 +66,13 @@ __device__ __forceinline__ int hist_bin(Real w, const Spec& sp, Real lnorm2) {
 
 // General reduction (Spec kinds) of NE transformed values: the sum of their
 // terms in FP64, or (histogram; HIST) a count in the block's LDS bins and 0.
-//  GEN_PLAIN    w = |W|^2 of one Pauli string per value
-//  GEN_HERM     the parts stand for two strings with |W| = 2 |Re| and 2 |Im|
-//  GEN_SQUARES  the parts are two values of W
+//  GEN_PLAIN  w = |W|^2 of one Pauli string per value
+//  GEN_HERM   the parts stand for two strings with |W| = 2 |Re| and 2 |Im|
 // Terms are free of branches (w that are not positive are selected away), one
 // loop per kind.  alpha = 3 and 4 are products in FP64 of w: two or three
 // operations instead of about 30 (FP32; FP64: far more) for
 // exp2(alpha log2 w), and more accurate (N = 15 FP32: 2.0 -> 0.75 ms).
-enum GenForm { GEN_PLAIN, GEN_HERM, GEN_SQUARES };
+enum GenForm { GEN_PLAIN, GEN_HERM };
 template <typename Real, int FORM, bool HIST, int NE, typename C>
 __device__ __forceinline__ double gen_sum(const C (&v)[NE], const Spec& sp, Real lnorm2,
                                           unsigned* __restrict__ lh) {
@@ -88,10 +89,8 @@ __device__ __forceinline__ double gen_sum(const C (&v)[NE], const Spec& sp, Real
             asm volatile("" : "+v"(x), "+v"(y));
             if constexpr (FORM == GEN_PLAIN)
                 acc += term(x * x + y * y);
-            else if constexpr (FORM == GEN_HERM)
-                acc += term(f * x * x) + term(f * y * y);
             else
-                acc += term(x * x) + term(y * y);
+                acc += term(f * x * x) + term(f * y * y);
         }
     };
     constexpr std::integral_constant<int, 4> four{};
@@ -99,8 +98,9 @@ __device__ __forceinline__ double gen_sum(const C (&v)[NE], const Spec& sp, Real
     // not positive or NaN: 0
     const auto wide = [](Real w) { return (double)(w > Real(0) ? w : Real(0)); };
     if (HIST && sp.kind == kRedHist) {
+        const int copy = threadIdx.x & (kHistCopies - 1);
         over(four, [&](Real w) {
-            atomicAdd(&lh[hist_bin<Real>(w, sp, lnorm2)], 1u);
+            atomicAdd(&lh[hist_bin<Real>(w, sp, lnorm2) * kHistCopies + copy], 1u);
             return 0.0;
         });
     } else if (sp.kind == kRedShannon) {
@@ -130,19 +130,25 @@ __device__ __forceinline__ double gen_sum(const C (&v)[NE], const Spec& sp, Real
     return acc;
 }
 
-// Block-level histogram bins: cleared at kernel start, added to the global
-// counters at the end (GEN kernels with a histogram Spec only).
+// Block-level histogram bins (GEN kernels with a histogram Spec only): cleared
+// at kernel start, added to the global counters at the end.  A state's values
+// crowd into a few bins, so that with one counter per bin the lanes of a wave
+// queue at the same address (67 M counts at N = 13: about 70 us); each bin has
+// kHistCopies counters, neighbouring lanes taking neighbouring ones.
 __device__ __forceinline__ void hist_clear(unsigned* lh, const Spec& sp) {
     if (sp.kind == kRedHist) {
-        for (int i = threadIdx.x; i < kMaxBins; i += blockDim.x) lh[i] = 0u;
+        for (int i = threadIdx.x; i < kMaxBins * kHistCopies; i += blockDim.x) lh[i] = 0u;
         __syncthreads();
     }
 }
 __device__ __forceinline__ void hist_flush(unsigned* lh, const Spec& sp) {
     if (sp.kind == kRedHist) {
         __syncthreads();
-        for (int i = threadIdx.x; i < sp.nbins; i += blockDim.x)
-            if (lh[i]) atomicAdd(&sp.hist[i], (unsigned long long)lh[i]);
+        for (int i = threadIdx.x; i < sp.nbins; i += blockDim.x) {
+            unsigned n = 0;
+            for (int c = 0; c < kHistCopies; ++c) n += lh[i * kHistCopies + c];
+            if (n) atomicAdd(&sp.hist[i], (unsigned long long)n);
+        }
     }
 }
 template <typename Real>

@@ -1,6 +1,5 @@
 // sre2_fused.hip - whole transforms on chip: k_tiny and k_fused (N below the
-// half transforms; the split forms and the Pauli spectrum up to the largest
-// tile), and the launcher of every on-chip shift sum.
+// half transforms; the split forms up to the largest tile), and the launcher of every on-chip shift sum.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -22,7 +21,7 @@ __global__ __launch_bounds__(64) void k_tiny(const typename CT<Real>::T* __restr
                                              const Pack pk, const Spec sp) {
     using C = typename CT<Real>::T;
     constexpr int D = 1 << N;
-    __shared__ unsigned lh[GEN ? kMaxBins : 1];
+    __shared__ unsigned lh[GEN ? kMaxBins * kHistCopies : 1];
     if constexpr (GEN) {
         hist_clear(lh, sp);
         const Real lnorm2 = hist_lnorm2<Real>(sp);
@@ -63,7 +62,7 @@ __host__ __device__ constexpr bool fused_keeps_psi(int NT, bool herm) {
 
 // ---------------------------------------------------------------------------
 // Fused: whole transforms of NT bits in a 2^TB tile of SPT = 2^(TB-NT) shifts.
-// From N = 12 (FP64: 11) on only the split forms and the spectrum take it: the
+// From N = 12 (FP64: 11) on only the split forms take it: the
 // half transforms of k_half do half the work and hold twice the waves (N = 14
 // FP32 450 -> 147 us, N = 13 FP64 142 -> 90 us per evaluation).
 //  HERM = false: NT = N, the tile element (slot j, k) is f_x(k), x = x0 + j.
@@ -97,7 +96,7 @@ void k_fused(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int6
     constexpr int NRED = (1 << (TB - RB)) * (int)sizeof(double) / (int)sizeof(C);
     constexpr int NL = lds_values(P);
     __shared__ C lds[NL > NRED ? NL : NRED];
-    __shared__ unsigned lh[GEN ? kMaxBins : 1];
+    __shared__ unsigned lh[GEN ? kMaxBins * kHistCopies : 1];
     double* red = reinterpret_cast<double*>(lds);
     if (pk.count) {
         psi = (const C*)pk.psi[blockIdx.y];
@@ -289,10 +288,8 @@ template <typename Real, bool GEN>
 hipError_t shift_kernel_gen(const void* psi, int N, bool herm, int split, int64_t x0,
                             int64_t xc, double* S, const int* se, const Pack& pk, const Spec& sp,
                             hipStream_t st) {
-    // From HMIN on the plain and Hermitian tiles serve the histogram only (the
-    // half transforms take the rest)
-    constexpr int RB = Tune<Real>::RBF;
-    constexpr int FMAX = GEN ? Tune<Real>::FMAX : Tune<Real>::HMIN - 1;
+    // from HMIN on the half transforms take the plain and Hermitian forms
+    constexpr int RB = Tune<Real>::RBF, FMAX = Tune<Real>::HMIN - 1;
     if (herm) {
         if (x0 < 1 || N - 1 < RB) return hipErrorInvalidValue;
         return dispatch_fused<Real, true, 0, GEN>(N - 1, psi, x0, xc, S, se, pk, sp, st,
@@ -317,7 +314,8 @@ hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int
                                int64_t xc, double* S, const int* se, const Pack& pk,
                                const Spec* sp, hipStream_t st) {
     const bool hist = sp && sp->kind == kRedHist;
-    const bool half = herm && !hist && N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX;
+    const bool half = !split && N >= Tune<Real>::HMIN &&
+                      N <= (hist ? half_hist_max<Real>() : Tune<Real>::HMAX);
     if ((N > Tune<Real>::FMAX && !half) || split < 0 || split > 2 ||
         (split && (herm || sizeof(Real) != 4)) || pk.count > kMaxPack)
         return hipErrorInvalidValue;
@@ -326,7 +324,7 @@ hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int
             (hist && (!sp->hist || !sp->nrm || sp->nbins < 2 || sp->nbins > kMaxBins)))
             return hipErrorInvalidValue;
     }
-    if (half) return launch_half<Real>(psi, N, x0, xc, S, pk, sp, st);
+    if (half) return launch_half<Real>(psi, N, herm, x0, xc, S, pk, sp, st);
     if (sp)
         return shift_kernel_gen<Real, true>(psi, N, herm, split, x0, xc, S, se, pk, *sp, st);
     return shift_kernel_gen<Real, false>(psi, N, herm, split, x0, xc, S, se, pk, Spec{}, st);

@@ -188,6 +188,13 @@ template <typename Real>
 constexpr int half_first(int N) {
     return sizeof(Real) == 4 && N > Tune<Real>::FMAX ? 1 : 0;
 }
+// Largest N whose histogram the half transforms take: the FP32 counts depend
+// on every rounding, so there the order of stages has to be the plain
+// transform's, which above the fused range is that of the two passes.
+template <typename Real>
+constexpr int half_hist_max() {
+    return sizeof(Real) == 4 ? Tune<Real>::FMAX : Tune<Real>::HMAX;
+}
 template <typename Real>
 constexpr int pass2_tb(int H) {
     const int want = H + Tune<Real>::P2COLS;

@@ -126,17 +126,36 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // Waves per SIMD asked of the compiler: with 64 registers of values per thread
 // four fit (128 registers each), with 128 (FP64 N = 14, 15) two.
+// (The histogram's terms spill a few words at four; three waves without spills
+// are slower: 163 against 151 us at N = 13 FP32.)
 template <typename Real>
 __host__ __device__ constexpr int half_waves_per_simd(int rb) {
     return (1 << rb) * (int)sizeof(Real) > 128 ? 2 : 4;
 }
 
-// Block b of the grid takes shift x_begin + b.
-template <typename Real, int NT, int RB, bool GEN>
+// Blocks of a histogram launch: each adds its bins to the global counters once
+// (one block per shift would queue 2^N of them at the same few addresses).
+constexpr int kHistBlocks = 2048;
+
+// Reductions: the sum of |W|^4, the general sums, the histogram.
+enum HalfRed { RED_QUARTIC, RED_GEN, RED_HIST };
+
+// Which set bit of x is left out (hb).  Any gives S_x.  HB_TOP: the top one.
+// HB_LAST: the one the plain transform of 2^N values butterflies last (its
+// order: the top five bits, the low five, the rest upwards).  With the others
+// transformed in that same order, every later bit is clear in x, so the pair
+// k, k ^ x meets element by element at its stage, whose results are exactly
+// (2 Re, 0) and (0, 2 Im): the values keep every bit of the plain transform,
+// which is what the counts of the plain forms' histogram depend on.
+enum HalfBit { HB_TOP, HB_LAST };
+
+// Block b of the grid takes shift x_begin + b, and with RED_HIST every
+// gridDim.x-th one from there (so that few blocks add to the global counters).
+template <typename Real, int NT, int RB, int RED>
 __global__ __launch_bounds__(1 << (NT - RB))
 __attribute__((amdgpu_waves_per_eu(half_waves_per_simd<Real>(RB))))
-void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin,
-            double* __restrict__ S_out, const Pack pk, const Spec sp) {
+void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64_t x_count,
+            double* __restrict__ S_out, const Pack pk, const Spec sp, int bit) {
     using C = typename CT<Real>::T;
     using HR = HalfRunner<Real, NT, RB, 1>;
     constexpr int N = NT + 1;
@@ -144,106 +163,145 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin,
     constexpr int NE = 1 << RB;
     constexpr Round r0 = HR::P.r[0];
     // bit of k that packs the halves of shift 0: the one the plain transform
-    // (top five bits, low five, the rest upwards) takes last
+    // takes last
     constexpr uint32_t HB0 = N - 6;
     __shared__ Real lds[HR::NV];
     __shared__ double red[NW];
+    __shared__ unsigned lh[RED == RED_HIST ? kMaxBins * kHistCopies : 1];
     if (pk.count) {
         psi = (const C*)pk.psi[blockIdx.y];
         S_out = pk_sx(pk.ws[blockIdx.y], N) + x_begin;
     }
-    const auto rs = buf_rsrc(psi, (uint32_t)sizeof(C) << N);
-    const uint32_t x = (uint32_t)x_begin + blockIdx.x;
-    const bool zero = x == 0;
-    const uint32_t base = thread_base<r0.lperm, r0.wave>();
-    C v[NE];
-    if (zero) {
-        // a rolled loop through the thread's own LDS slots, so that one
-        // workgroup's case does not cost the others registers
-        static_assert(r0.reg == top_bits(bits_range(0, NT), RB), "element bits of a register");
-        const auto squares = [&](uint32_t bit) {
-#pragma unroll 1
-            for (uint32_t i = 0; i < NE; ++i) {
-                const uint32_t e = base | (i << (NT - RB));
-                const C c = load_at<C>(rs, insert0(e, HB0) | bit, 0);
-                lds[pad16<5>(e)] = cmul_conj_a(c, c).x;
-            }
-        };
-        squares(0u);
-        lds_part<false, 0, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
-        squares(1u << HB0);
-        lds_part<false, 1, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
-    } else {
-        // element e -> k = insert0(e, hb), and the partner k ^ x; insert0 and
-        // the XOR act on disjoint bits of the thread's and the register's part
-        // of e, so the register's part of an address is uniform (a scalar
-        // offset)
-        const uint32_t hb = 31u - __clz(x);
-        const uint32_t R = insert0(r0.reg, hb);
-        const uint32_t kb = insert0(base, hb);
-        const uint32_t vb = kb ^ (x & ~R), xr = x & R;
-#pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const uint32_t kr = insert0(pdep((uint32_t)i, r0.reg), hb);
-            v[i] = cmul_conj_f(load_at<C>(rs, vb, kr ^ xr), load_at<C>(rs, kb, kr));
-        }
+    Real lnorm2 = Real(0);
+    if constexpr (RED == RED_HIST) {
+        hist_clear(lh, sp);
+        lnorm2 = hist_lnorm2<Real>(sp);
     }
-    butterflies<RB, r0.reg, r0.bfly>(v);
-    HR::run(lds, v);
-    double acc = 0.0;
-    if (zero) {  // the last stage, across the two halves
-#pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const Real a = v[i].x + v[i].y, c = v[i].x - v[i].y;
-            v[i].x = a;
-            v[i].y = c;
-        }
-        if constexpr (GEN) {
-            acc = gen_sum<Real, GEN_SQUARES, false>(v, sp, Real(0), nullptr);
+    const auto rs = buf_rsrc(psi, (uint32_t)sizeof(C) << N);
+    const uint32_t base = thread_base<r0.lperm, r0.wave>();
+    const auto one_shift = [&](uint32_t at) {
+        const uint32_t x = (uint32_t)x_begin + at;
+        const bool zero = x == 0;
+        C v[NE];
+        if (zero) {
+            // a rolled loop through the thread's own LDS slots, so that one
+            // workgroup's case does not cost the others registers
+            static_assert(r0.reg == top_bits(bits_range(0, NT), RB), "element bits of a register");
+            const auto squares = [&](uint32_t half) {
+#pragma unroll 1
+                for (uint32_t i = 0; i < NE; ++i) {
+                    const uint32_t e = base | (i << (NT - RB));
+                    const C c = load_at<C>(rs, insert0(e, HB0) | half, 0);
+                    lds[pad16<5>(e)] = cmul_conj_a(c, c).x;
+                }
+            };
+            squares(0u);
+            lds_part<false, 0, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
+            squares(1u << HB0);
+            lds_part<false, 1, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
         } else {
+            // element e -> k, the map putting a zero at bit hb, and the partner
+            // k ^ x; both act on disjoint bits of the thread's and the
+            // register's part of e, so the register's part of an address is
+            // uniform (a scalar offset)
+            uint32_t hb = 31u - __clz(x);
+            bool top5 = false;
+            if constexpr (RED == RED_HIST) {
+                const uint32_t mid = x & bits_range(5, N - 5), low = x & 31u;
+                if (bit == HB_LAST && (mid | low)) hb = 31u - __clz(mid ? mid : low);
+                top5 = bit == HB_LAST && !(mid | low);
+            }
+            const auto k_of = [&](uint32_t e) {
+                if constexpr (RED == RED_HIST) {
+                    // x has top bits only: the first round keeps the other
+                    // four and takes bit 0 as its last
+                    if (top5)
+                        return ((e << 1) & bits_range(1, N - 5)) |
+                               insert0(((e >> (N - 6)) & 15u) << (N - 5), hb) | (e >> (N - 2));
+                }
+                return insert0(e, hb);
+            };
+            const uint32_t R = k_of(r0.reg);
+            const uint32_t kb = k_of(base);
+            const uint32_t vb = kb ^ (x & ~R), xr = x & R;
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const uint32_t kr = k_of(pdep((uint32_t)i, r0.reg));
+                if constexpr (RED == RED_HIST)
+                    v[i] = cmul_conj_a(load_at<C>(rs, vb, kr ^ xr), load_at<C>(rs, kb, kr));
+                else
+                    v[i] = cmul_conj_f(load_at<C>(rs, vb, kr ^ xr), load_at<C>(rs, kb, kr));
+            }
+        }
+        butterflies<RB, r0.reg, r0.bfly>(v);
+        HR::run(lds, v);
+        double acc = 0.0;
+        if (zero) {
+            // the last stage, across the two halves: two values of W, halved
+            // (exactly) to go through the same sum as 2 Re and 2 Im
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const Real a = v[i].x + v[i].y, c = v[i].x - v[i].y;
+                v[i].x = Real(0.5) * a;
+                v[i].y = Real(0.5) * c;
+            }
+        }
+        if constexpr (RED == RED_QUARTIC) {
 #pragma unroll
             for (int i = 0; i < NE; ++i) acc += abs4h(v[i]);
+            acc *= 16.0;
+        } else {
+            acc = gen_sum<Real, GEN_HERM, RED == RED_HIST>(v, sp, lnorm2, lh);
         }
-    } else if constexpr (GEN) {
-        acc = gen_sum<Real, GEN_HERM, false>(v, sp, Real(0), nullptr);
-    } else {
-#pragma unroll
-        for (int i = 0; i < NE; ++i) acc += abs4h(v[i]);
-        acc *= 16.0;
-    }
-    acc = wave_sum(acc);
-    if constexpr (NW == 1) {
-        if (threadIdx.x == 0) S_out[blockIdx.x] = acc;
-    } else {
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) t += red[w];
-            S_out[blockIdx.x] = t;
+        if constexpr (RED == RED_HIST) {  // its sum is 0 in every shift
+            if (threadIdx.x == 0) S_out[at] = acc;
+            return;
         }
+        acc = wave_sum(acc);
+        if constexpr (NW == 1) {
+            if (threadIdx.x == 0) S_out[at] = acc;
+        } else {
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double t = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) t += red[w];
+                S_out[at] = t;
+            }
+        }
+    };
+    if constexpr (RED == RED_HIST) {
+        for (uint32_t at = blockIdx.x; at < (uint32_t)x_count; at += gridDim.x) {
+            __syncthreads();  // the previous shift's readers of the buffer
+            one_shift(at);
+        }
+        hist_flush(lh, sp);
+    } else {
+        one_shift(blockIdx.x);
     }
 }
 
-template <typename Real, int N, bool GEN>
+template <typename Real, int N, int RED>
 hipError_t launch_half_n(const void* psi, int64_t x0, int64_t xc, double* S, const Pack& pk,
-                         const Spec& sp, hipStream_t st) {
+                         const Spec& sp, int bit, hipStream_t st) {
     using C = typename CT<Real>::T;
     constexpr int RB = half_rb<Real>(N);
-    hipLaunchKernelGGL((k_half<Real, N - 1, RB, GEN>),
-                       dim3((unsigned)xc, (unsigned)(pk.count ? pk.count : 1)),
-                       dim3(1 << (N - 1 - RB)), 0, st, (const C*)psi, x0, S, pk, sp);
+    const int64_t blocks = RED == RED_HIST && xc > kHistBlocks ? kHistBlocks : xc;
+    hipLaunchKernelGGL((k_half<Real, N - 1, RB, RED>),
+                       dim3((unsigned)blocks, (unsigned)(pk.count ? pk.count : 1)),
+                       dim3(1 << (N - 1 - RB)), 0, st, (const C*)psi, x0, xc, S, pk, sp, bit);
     return hipGetLastError();
 }
 
-template <typename Real, bool GEN, int... Ns>
+template <typename Real, int RED, int... Ns>
 hipError_t dispatch_half(int N, const void* psi, int64_t x0, int64_t xc, double* S,
-                         const Pack& pk, const Spec& sp, hipStream_t st,
+                         const Pack& pk, const Spec& sp, int bit, hipStream_t st,
                          std::integer_sequence<int, Ns...>) {
     hipError_t e = hipErrorInvalidValue;
     ((N == Ns + Tune<Real>::HMIN
-          ? (e = launch_half_n<Real, Ns + Tune<Real>::HMIN, GEN>(psi, x0, xc, S, pk, sp, st), 0)
+          ? (e = launch_half_n<Real, Ns + Tune<Real>::HMIN, RED>(psi, x0, xc, S, pk, sp, bit, st),
+             0)
           : 0),
      ...);
     return e;
@@ -252,18 +310,24 @@ hipError_t dispatch_half(int N, const void* psi, int64_t x0, int64_t xc, double*
 }  // namespace
 
 template <typename Real>
-hipError_t launch_half(const void* psi, int N, int64_t x0, int64_t xc, double* S, const Pack& pk,
-                       const Spec* sp, hipStream_t st) {
-    if (N < Tune<Real>::HMIN || N > Tune<Real>::HMAX || xc < 1 || x0 < (half_first<Real>(N)) ||
-        x0 + xc > ((int64_t)1 << N))
+hipError_t launch_half(const void* psi, int N, bool herm, int64_t x0, int64_t xc, double* S,
+                       const Pack& pk, const Spec* sp, hipStream_t st) {
+    const bool hist = sp && sp->kind == kRedHist;
+    if (N < Tune<Real>::HMIN || N > (hist ? half_hist_max<Real>() : Tune<Real>::HMAX) || xc < 1 ||
+        x0 < half_first<Real>(N) || x0 + xc > ((int64_t)1 << N))
         return hipErrorInvalidValue;
     constexpr auto ns = std::make_integer_sequence<int, Tune<Real>::HMAX - Tune<Real>::HMIN + 1>{};
-    if (sp) return dispatch_half<Real, true>(N, psi, x0, xc, S, pk, *sp, st, ns);
-    return dispatch_half<Real, false>(N, psi, x0, xc, S, pk, Spec{}, st, ns);
+    constexpr auto hs =
+        std::make_integer_sequence<int, half_hist_max<Real>() - Tune<Real>::HMIN + 1>{};
+    if (hist)
+        return dispatch_half<Real, RED_HIST>(N, psi, x0, xc, S, pk, *sp,
+                                             herm || sizeof(Real) == 8 ? HB_TOP : HB_LAST, st, hs);
+    if (sp) return dispatch_half<Real, RED_GEN>(N, psi, x0, xc, S, pk, *sp, HB_TOP, st, ns);
+    return dispatch_half<Real, RED_QUARTIC>(N, psi, x0, xc, S, pk, Spec{}, HB_TOP, st, ns);
 }
-template hipError_t launch_half<float>(const void*, int, int64_t, int64_t, double*, const Pack&,
-                                       const Spec*, hipStream_t);
-template hipError_t launch_half<double>(const void*, int, int64_t, int64_t, double*, const Pack&,
-                                        const Spec*, hipStream_t);
+template hipError_t launch_half<float>(const void*, int, bool, int64_t, int64_t, double*,
+                                       const Pack&, const Spec*, hipStream_t);
+template hipError_t launch_half<double>(const void*, int, bool, int64_t, int64_t, double*,
+                                        const Pack&, const Spec*, hipStream_t);
 
 }  // namespace sre2

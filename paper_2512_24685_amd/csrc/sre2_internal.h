@@ -79,15 +79,17 @@ template <typename Real> int herm_min_n();
 // groups P).
 template <typename Real> int64_t pass2_col_tiles(int N, int slab);
 
-// N evaluated on chip by half transforms (all forms but the split ones, all
-// reductions but the histogram), and the first shift they take there (0, or
-// 1 where shift 0 goes through the two-pass kernels).
-template <typename Real> bool half_takes(int N);
+// Row bits up to which pass 2 is a single round.
+template <typename Real> int pass2_round_bits();
+// N evaluated on chip by half transforms (all forms but the split ones; hist:
+// for the histogram), and the first shift they take there (0, or 1 where shift
+// 0 goes through the two-pass kernels).
+template <typename Real> bool half_takes(int N, bool hist);
 template <typename Real> int half_first_shift(int N);
 
-// S[i] = S_{x0+i} for shifts [x0, x0 + xc): with herm, the half transforms
-// where half_takes(N) (not for the histogram); else the tiny kernel (plain,
-// N < RB) or the fused kernel (N <= fused_max_n).  `split` selects the split MFMA transform
+// S[i] = S_{x0+i} for shifts [x0, x0 + xc): the half transforms where they take
+// N (herm: a Hermitian-pair form); else the tiny kernel (plain, N < RB) or the
+// fused kernel (N <= fused_max_n).  `split` selects the split MFMA transform
 // (0 none, 1 FP16 halves, 2 BF16 halves; FP32 only, not with herm); it reads
 // the scale exponent *se.
 // With pk.count > 0 the launch covers pk.count states of the same N (grid
@@ -97,10 +99,9 @@ template <typename Real>
 hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int64_t x0,
                                int64_t xc, double* S, const int* se, const Pack& pk,
                                const Spec* sp, hipStream_t st);
-// The half transforms of launch_shift_kernel (half_takes(N), x0 >=
-// half_first_shift(N), sp not a histogram).
+// The half transforms of launch_shift_kernel (x0 >= half_first_shift(N)).
 template <typename Real>
-hipError_t launch_half(const void* psi, int N, int64_t x0, int64_t xc, double* S, const Pack& pk,
+hipError_t launch_half(const void* psi, int N, bool herm, int64_t x0, int64_t xc, double* S, const Pack& pk,
                        const Spec* sp, hipStream_t st);
 // Two-pass slab kinds: the full slab of 2^N values per shift; the Hermitian
 // pair's half slab (2^(N-1) values, rows of pass1_row_bits(N - 1) bits); the

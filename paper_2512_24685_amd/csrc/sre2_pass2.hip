@@ -63,7 +63,7 @@ void k_pass2(const typename CT<Real>::T* __restrict__ scratch, int NS, int P,
     constexpr bool NT = SRE2_NT_SLAB && ((int)sizeof(C) << CB) >= 128;
     __shared__ C lds[lds_values(PL)];
     __shared__ double red[T];
-    __shared__ unsigned lh[GEN ? kMaxBins : 1];
+    __shared__ unsigned lh[GEN ? kMaxBins * kHistCopies : 1];
     Real lnorm2 = Real(0);
     if constexpr (GEN) {
         hist_clear(lh, sp);

@@ -32,15 +32,20 @@ int64_t pass2_col_tiles(int N, int slab) {
     return tb > 0 ? (int64_t)1 << (L + HT - tb) : 0;
 }
 template <typename Real>
-bool half_takes(int N) {
-    return N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX;
+int pass2_round_bits() {
+    return Tune<Real>::RB2;
+}
+template int pass2_round_bits<float>();
+template <typename Real>
+bool half_takes(int N, bool hist) {
+    return N >= Tune<Real>::HMIN && N <= (hist ? half_hist_max<Real>() : Tune<Real>::HMAX);
 }
 template <typename Real>
 int half_first_shift(int N) {
     return half_first<Real>(N);
 }
-template bool half_takes<float>(int);
-template bool half_takes<double>(int);
+template bool half_takes<float>(int, bool);
+template bool half_takes<double>(int, bool);
 template int half_first_shift<float>(int);
 template int half_first_shift<double>(int);
 template int max_n<float>();

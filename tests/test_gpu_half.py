@@ -67,3 +67,25 @@ def test_packed_states_equal_single_calls(form, N):
     for p, b in zip(psis, sre2.m2_batched(psis, form=form)):
         a = sre2.m2(p, form=form)
         assert a.m2 == b.m2 and a.S == b.S and b.status == 0
+
+
+@pytest.mark.parametrize("form,N", [("fp32", 12), ("fp32", 14), ("fp32", 15), ("fp32", 17),
+                                    ("fp32h", 13), ("fp64", 11), ("fp64", 15)])
+def test_spectrum_counts_are_the_plain_transforms(oracle_mod, form, N):
+    """Every shift of |T>^N has its values at 0 and n 2^-popcount(...): exact
+    counts C(N, k) 2^k whichever bit a half transform leaves out (shift 0, the
+    shifts of the top five bits, low bits, middle bits); a Haar state's counts
+    against the oracle, up to the strings near a bin edge."""
+    from math import comb
+    c128 = form.startswith("fp64")
+    dt = np.complex128 if c128 else np.complex64
+    print("CASE half spectrum", form, N, flush=True)
+    counts, _ = sre2.pauli_spectrum(dev(W.t_product(N, dt)), N + 3, form=form)
+    for k in range(N + 1):
+        assert counts[k] == comb(N, k) * 2 ** k
+    assert counts.sum() == 4 ** N
+    if N <= 14:
+        psi = W.haar(N, 4400 + N, dt)
+        counts, _ = sre2.pauli_spectrum(dev(psi), N + 6, form=form)
+        ref, near = oracle_mod.spectrum(psi, N + 6, eps=2e-3 if not c128 else 1e-7)
+        assert int(np.abs(counts - ref).sum()) <= 2 * near
