@@ -102,13 +102,9 @@ bool half_path(int N, int form, const Spec* spec) {
     return !is_split(form) &&
            (is_f64(form) ? half_takes<double>(N, hist) : half_takes<float>(N, hist));
 }
-int half_first(int N, int form) {
-    return is_f64(form) ? half_first_shift<double>(N) : half_first_shift<float>(N);
-}
-// Shifts of [x0, x0 + xc) that go through the two-pass kernels (from x0 on).
-int64_t two_pass_shifts(int N, int form, bool half, int64_t x0, int64_t xc) {
-    if (half) return x0 < half_first(N, form) ? half_first(N, form) - x0 : 0;
-    return N <= fused_max(form) ? 0 : xc;
+// The evaluation goes through the two-pass kernels.
+bool two_pass_path(int N, int form, const Spec* spec) {
+    return N > fused_max(form) && !half_path(N, form, spec);
 }
 int64_t col_tiles(int N, int form, int slab) {
     return is_f64(form) ? pass2_col_tiles<double>(N, slab) : pass2_col_tiles<float>(N, slab);
@@ -333,8 +329,7 @@ int ctx_two_pass_ws(sre2_ctx* ctx, int N, int form, int64_t x0, int64_t xc, cons
                     Workspace* ws) {
     ws->pairs = ctx->row_pairs;
     const int high = high_slab(N, form, ws->pairs, spec);
-    xc = two_pass_shifts(N, form, half_path(N, form, spec), x0, xc);
-    if (xc == 0) return SRE2_OK;
+    if (!two_pass_path(N, form, spec)) return SRE2_OK;
     size_t limit = ctx->scratch_limit, need = 0, need_part = 0;
     int rc;
     for (;;) {
@@ -362,18 +357,12 @@ int shift_sums(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int
     const bool f64 = is_f64(form);
     const int sp = split_kind(form);
     if (half_path(N, form, spec)) {
-        const int64_t two = two_pass_shifts(N, form, true, x0, xc);
-        if (two) {
-            const int rc = two_pass(tctx, ws, work, N, form, kSlabFull, x0, two, Sx, se, spec, st);
-            if (rc) return rc;
-        }
-        if (xc == two) return SRE2_OK;
         Timed tm(tctx, st, SRE2_KIND_SHIFT);
         const bool herm = is_herm(form);
-        return hip_status(f64 ? launch_shift_kernel<double>(work, N, herm, 0, x0 + two, xc - two,
-                                                            Sx + two, se, Pack{}, spec, st)
-                              : launch_shift_kernel<float>(work, N, herm, 0, x0 + two, xc - two,
-                                                           Sx + two, se, Pack{}, spec, st));
+        return hip_status(f64 ? launch_shift_kernel<double>(work, N, herm, 0, x0, xc, Sx, se,
+                                                            Pack{}, spec, st)
+                              : launch_shift_kernel<float>(work, N, herm, 0, x0, xc, Sx, se,
+                                                           Pack{}, spec, st));
     }
     const int64_t x1 = x0 + xc;
     if (N <= fused_max(form)) {
@@ -582,12 +571,12 @@ int ws_layout(int N, int dtype, int form, bool need_sx, size_t bytes, size_t* ps
         off = up(off + n * sizeof(double));
     }
     if (off > bytes) return SRE2_ESCRATCH;
-    const int64_t xc = two_pass_shifts(N, form, half_path(N, form, nullptr), 0, (int64_t)n);
-    if (xc == 0) return SRE2_OK;
+    if (!two_pass_path(N, form, nullptr)) return SRE2_OK;
     // the largest chunks whose slab and partials fit what is left
     size_t lim = bytes - off, need = 0, need_part = 0;
     for (;;) {
-        const int64_t cs = slab_need(N, form, high_slab(N, form, true, nullptr), 0, xc, lim, &need, &need_part);
+        const int64_t cs = slab_need(N, form, high_slab(N, form, true, nullptr), 0, (int64_t)n, lim,
+                                      &need, &need_part);
         const size_t pb = up(need_part * sizeof(double));
         if (off + pb + need <= bytes) {
             *part_off = off;

@@ -62,7 +62,7 @@ __host__ __device__ constexpr bool fused_keeps_psi(int NT, bool herm) {
 
 // ---------------------------------------------------------------------------
 // Fused: whole transforms of NT bits in a 2^TB tile of SPT = 2^(TB-NT) shifts.
-// From N = 12 (FP64: 11) on only the split forms take it: the
+// From N = 11 on only the split forms take it (and the FP32 spectrum of N = 11): the
 // half transforms of k_half do half the work and hold twice the waves (N = 14
 // FP32 450 -> 147 us, N = 13 FP64 142 -> 90 us per evaluation).
 //  HERM = false: NT = N, the tile element (slot j, k) is f_x(k), x = x0 + j.
@@ -288,8 +288,9 @@ template <typename Real, bool GEN>
 hipError_t shift_kernel_gen(const void* psi, int N, bool herm, int split, int64_t x0,
                             int64_t xc, double* S, const int* se, const Pack& pk, const Spec& sp,
                             hipStream_t st) {
-    // from HMIN on the half transforms take the plain and Hermitian forms
-    constexpr int RB = Tune<Real>::RBF, FMAX = Tune<Real>::HMIN - 1;
+    // above FMAX the half transforms take the plain and Hermitian forms
+    constexpr int RB = Tune<Real>::RBF;
+    constexpr int FMAX = (GEN ? half_hist_min<Real>() : Tune<Real>::HMIN) - 1;
     if (herm) {
         if (x0 < 1 || N - 1 < RB) return hipErrorInvalidValue;
         return dispatch_fused<Real, true, 0, GEN>(N - 1, psi, x0, xc, S, se, pk, sp, st,
@@ -314,8 +315,8 @@ hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int
                                int64_t xc, double* S, const int* se, const Pack& pk,
                                const Spec* sp, hipStream_t st) {
     const bool hist = sp && sp->kind == kRedHist;
-    const bool half = !split && N >= Tune<Real>::HMIN &&
-                      N <= (hist ? half_hist_max<Real>() : Tune<Real>::HMAX);
+    const bool half = !split && (hist ? N >= half_hist_min<Real>() && N <= half_hist_max<Real>()
+                                      : N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX);
     if ((N > Tune<Real>::FMAX && !half) || split < 0 || split > 2 ||
         (split && (herm || sizeof(Real) != 4)) || pk.count > kMaxPack)
         return hipErrorInvalidValue;

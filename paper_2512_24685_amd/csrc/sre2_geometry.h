@@ -77,7 +77,7 @@ constexpr int kMaxNAll = 26;
 // HMAX: the half transform fills the register file of a CU (1024 threads of
 // 64 or 512 of 128 value registers) and its real parts 128 KiB of LDS.
 #ifndef SRE2_F32_HALF_MIN
-#define SRE2_F32_HALF_MIN 12
+#define SRE2_F32_HALF_MIN 11
 #endif
 #ifndef SRE2_F64_HALF_MIN
 #define SRE2_F64_HALF_MIN 11
@@ -173,20 +173,22 @@ constexpr int fused_rb(int N, bool split) {
                 ? (sizeof(Real) == 4 ? SRE2_F32_FUSED_HALF_RB : SRE2_F64_FUSED_HALF_RB)
                 : 0);
 }
-// Registers (log2 of complex values) per thread of a half transform.  FP32: 32
-// values (16: 174 against 163 us at N = 14).  FP64: 16 values up to N = 13
-// (69 against 76 us with 32 there); 32 above, which saves a round where the
-// LDS leaves two or one workgroup per CU anyway (N = 14 283 against 306 us,
-// N = 15 1.55 against 1.76 ms).
+// Registers (log2 of complex values) per thread of a half transform.  FP32: 16
+// values up to N = 13 (N = 12 12.9 against 14.1 us with 32, N = 13 44 against
+// 48), 32 above, which saves a round (N = 14 163 against 174 us); 32 for the
+// histogram, whose stage order is that of the plain 32-value tiles.  FP64: 16
+// values up to N = 13 (69 against 76 us with 32 there); 32 above, which saves
+// a round where the LDS leaves two or one workgroup per CU anyway (N = 14 283
+// against 306 us, N = 15 1.55 against 1.76 ms).
 template <typename Real>
-constexpr int half_rb(int N) {
-    return sizeof(Real) == 4 ? 5 : (N <= 13 ? 4 : 5);
+constexpr int half_rb(int N, bool hist) {
+    return N <= 13 && !(hist && sizeof(Real) == 4) ? 4 : 5;
 }
-// First shift the half transforms take: 0, or 1 for FP32 sizes above the
-// fused range, whose shift 0 keeps the stage order of the two passes.
+// Smallest N whose histogram they take (a whole wave of threads).
 template <typename Real>
-constexpr int half_first(int N) {
-    return sizeof(Real) == 4 && N > Tune<Real>::FMAX ? 1 : 0;
+constexpr int half_hist_min() {
+    return half_rb<Real>(Tune<Real>::HMIN, true) + 6 > Tune<Real>::HMIN - 1 ? Tune<Real>::HMIN + 1
+                                                                            : Tune<Real>::HMIN;
 }
 // Largest N whose histogram the half transforms take: the FP32 counts depend
 // on every rounding, so there the order of stages has to be the plain

@@ -7,9 +7,9 @@
 // 2i Im A, and S_x = 16 sum (Re^4 + Im^4).  Shift 0 has no such pairing, but
 // f_0 = |psi|^2 is real: the two halves k_hb = 0 and 1 are carried as the real
 // and imaginary part of one complex transform, and one last stage A.re +- A.im
-// gives W_0.  Its stages run in the order of the plain transform of 2^N
-// values (top five bits, low five, the rest upwards), so that W_0, a quarter
-// of a Haar state's S, keeps its bits.
+// gives W_0.  Its bits are assigned so that its stages run in the order of the
+// plain transform of 2^N values, and W_0, a quarter of a Haar state's S, keeps
+// its bits.
 //
 // A workgroup holds one half transform of 2^(N-1) complex values in registers
 // and transposes it between rounds through an LDS buffer of one real part
@@ -133,6 +133,39 @@ __host__ __device__ constexpr int half_waves_per_simd(int rb) {
     return (1 << rb) * (int)sizeof(Real) > 128 ? 2 : 4;
 }
 
+// The order in which the plain transform of 2^N values butterflies its bits:
+// on chip the top five, the low five, the rest upwards; above (FP32) pass 1's
+// four top row bits of 12, its low four and the rest, then the column bits.
+struct BitOrder {
+    int bit[kMaxTileBits + 1] = {};
+};
+template <typename Real>
+__host__ __device__ constexpr BitOrder plain_order(int N) {
+    BitOrder o{};
+    const bool two = N > Tune<Real>::FMAX;
+    const int rows = two ? Tune<Real>::ROW : N, g = two ? Tune<Real>::RB1 : 5;
+    int n = 0;
+    for (int b = rows - g; b < rows; ++b) o.bit[n++] = b;
+    for (int b = 0; b < rows - g; ++b) o.bit[n++] = b;
+    for (int b = rows; b < N; ++b) o.bit[n++] = b;
+    return o;
+}
+// Shift 0: element bit e of the half transform (its j-th butterfly) is bit
+// plain_order[j] of k; the last of that order packs the halves into the real
+// and imaginary part.
+template <typename Real, int NT, int RB>
+__host__ __device__ constexpr BitOrder zero_map() {
+    constexpr Plan P = HalfRunner<Real, NT, RB, 1>::P;
+    constexpr BitOrder o = plain_order<Real>(NT + 1);
+    BitOrder m{};
+    int n = 0;
+    for (int r = 0; r < P.nrounds; ++r)
+        for (int b = 0; b < NT; ++b)
+            if ((P.r[r].bfly >> b) & 1u) m.bit[b] = o.bit[n++];
+    m.bit[NT] = o.bit[n];
+    return m;
+}
+
 // Blocks of a histogram launch: each adds its bins to the global counters once
 // (one block per shift would queue 2^N of them at the same few addresses).
 constexpr int kHistBlocks = 2048;
@@ -162,9 +195,7 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
     constexpr int NW = (1 << (NT - RB)) / 64;
     constexpr int NE = 1 << RB;
     constexpr Round r0 = HR::P.r[0];
-    // bit of k that packs the halves of shift 0: the one the plain transform
-    // takes last
-    constexpr uint32_t HB0 = N - 6;
+    static_assert(RED != RED_HIST || sizeof(Real) == 8 || RB == 5, "HB_LAST's stage order");
     __shared__ Real lds[HR::NV];
     __shared__ double red[NW];
     __shared__ unsigned lh[RED == RED_HIST ? kMaxBins * kHistCopies : 1];
@@ -187,17 +218,21 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
             // a rolled loop through the thread's own LDS slots, so that one
             // workgroup's case does not cost the others registers
             static_assert(r0.reg == top_bits(bits_range(0, NT), RB), "element bits of a register");
+            constexpr BitOrder map = zero_map<Real, NT, RB>();
             const auto squares = [&](uint32_t half) {
 #pragma unroll 1
                 for (uint32_t i = 0; i < NE; ++i) {
                     const uint32_t e = base | (i << (NT - RB));
-                    const C c = load_at<C>(rs, insert0(e, HB0) | half, 0);
+                    uint32_t q = half << map.bit[NT];
+#pragma unroll
+                    for (int b = 0; b < NT; ++b) q |= ((e >> b) & 1u) << map.bit[b];
+                    const C c = load_at<C>(rs, q, 0);
                     lds[pad16<5>(e)] = cmul_conj_a(c, c).x;
                 }
             };
             squares(0u);
             lds_part<false, 0, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
-            squares(1u << HB0);
+            squares(1u);
             lds_part<false, 1, RB, r0.reg, r0.lperm, r0.wave>(lds, v);
         } else {
             // element e -> k, the map putting a zero at bit hb, and the partner
@@ -286,7 +321,7 @@ template <typename Real, int N, int RED>
 hipError_t launch_half_n(const void* psi, int64_t x0, int64_t xc, double* S, const Pack& pk,
                          const Spec& sp, int bit, hipStream_t st) {
     using C = typename CT<Real>::T;
-    constexpr int RB = half_rb<Real>(N);
+    constexpr int RB = half_rb<Real>(N, RED == RED_HIST);
     const int64_t blocks = RED == RED_HIST && xc > kHistBlocks ? kHistBlocks : xc;
     hipLaunchKernelGGL((k_half<Real, N - 1, RB, RED>),
                        dim3((unsigned)blocks, (unsigned)(pk.count ? pk.count : 1)),
@@ -299,9 +334,9 @@ hipError_t dispatch_half(int N, const void* psi, int64_t x0, int64_t xc, double*
                          const Pack& pk, const Spec& sp, int bit, hipStream_t st,
                          std::integer_sequence<int, Ns...>) {
     hipError_t e = hipErrorInvalidValue;
-    ((N == Ns + Tune<Real>::HMIN
-          ? (e = launch_half_n<Real, Ns + Tune<Real>::HMIN, RED>(psi, x0, xc, S, pk, sp, bit, st),
-             0)
+    constexpr int N0 = RED == RED_HIST ? half_hist_min<Real>() : Tune<Real>::HMIN;
+    ((N == Ns + N0
+          ? (e = launch_half_n<Real, Ns + N0, RED>(psi, x0, xc, S, pk, sp, bit, st), 0)
           : 0),
      ...);
     return e;
@@ -313,12 +348,11 @@ template <typename Real>
 hipError_t launch_half(const void* psi, int N, bool herm, int64_t x0, int64_t xc, double* S,
                        const Pack& pk, const Spec* sp, hipStream_t st) {
     const bool hist = sp && sp->kind == kRedHist;
-    if (N < Tune<Real>::HMIN || N > (hist ? half_hist_max<Real>() : Tune<Real>::HMAX) || xc < 1 ||
-        x0 < half_first<Real>(N) || x0 + xc > ((int64_t)1 << N))
+    if (xc < 1 || x0 < 0 || x0 + xc > ((int64_t)1 << N))
         return hipErrorInvalidValue;
     constexpr auto ns = std::make_integer_sequence<int, Tune<Real>::HMAX - Tune<Real>::HMIN + 1>{};
     constexpr auto hs =
-        std::make_integer_sequence<int, half_hist_max<Real>() - Tune<Real>::HMIN + 1>{};
+        std::make_integer_sequence<int, half_hist_max<Real>() - half_hist_min<Real>() + 1>{};
     if (hist)
         return dispatch_half<Real, RED_HIST>(N, psi, x0, xc, S, pk, *sp,
                                              herm || sizeof(Real) == 8 ? HB_TOP : HB_LAST, st, hs);

@@ -82,10 +82,8 @@ template <typename Real> int64_t pass2_col_tiles(int N, int slab);
 // Row bits up to which pass 2 is a single round.
 template <typename Real> int pass2_round_bits();
 // N evaluated on chip by half transforms (all forms but the split ones; hist:
-// for the histogram), and the first shift they take there (0, or 1 where shift
-// 0 goes through the two-pass kernels).
+// for the histogram).
 template <typename Real> bool half_takes(int N, bool hist);
-template <typename Real> int half_first_shift(int N);
 
 // S[i] = S_{x0+i} for shifts [x0, x0 + xc): the half transforms where they take
 // N (herm: a Hermitian-pair form); else the tiny kernel (plain, N < RB) or the
@@ -99,7 +97,7 @@ template <typename Real>
 hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int64_t x0,
                                int64_t xc, double* S, const int* se, const Pack& pk,
                                const Spec* sp, hipStream_t st);
-// The half transforms of launch_shift_kernel (x0 >= half_first_shift(N)).
+// The half transforms of launch_shift_kernel.
 template <typename Real>
 hipError_t launch_half(const void* psi, int N, bool herm, int64_t x0, int64_t xc, double* S, const Pack& pk,
                        const Spec* sp, hipStream_t st);

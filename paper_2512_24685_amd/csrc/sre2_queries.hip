@@ -38,16 +38,11 @@ int pass2_round_bits() {
 template int pass2_round_bits<float>();
 template <typename Real>
 bool half_takes(int N, bool hist) {
-    return N >= Tune<Real>::HMIN && N <= (hist ? half_hist_max<Real>() : Tune<Real>::HMAX);
-}
-template <typename Real>
-int half_first_shift(int N) {
-    return half_first<Real>(N);
+    return hist ? N >= half_hist_min<Real>() && N <= half_hist_max<Real>()
+                : N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX;
 }
 template bool half_takes<float>(int, bool);
 template bool half_takes<double>(int, bool);
-template int half_first_shift<float>(int);
-template int half_first_shift<double>(int);
 template int max_n<float>();
 template int max_n<double>();
 template int fused_max_n<float>();
