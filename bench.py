@@ -152,11 +152,11 @@ def roofline(N, form, kind, ms, launches, traffic, evals=1, x0=0, xc=None):
                        hbm_GBs=round(gbs, 1), hbm_frac=round(gbs / HBM_PEAK_GBS, 4))
         return ent
     # on-chip kernels: every value stays on chip; VALU-bound.  The plain and
-    # Hermitian forms take half transforms from N = 11 on; below,
+    # Hermitian forms take half transforms from N = 10 on; below,
     # the Hermitian forms run x = 0 as a separate short plain launch, so the
     # work and the time are taken per evaluation (all launches of the class)
     # rather than per launch.
-    half = N >= 11 and not form.startswith("split")
+    half = N >= 10 and not form.startswith("split")
     herm = form.endswith("h") or half
     nt = N - (1 if herm else 0)
     ops = (4 + 2 * nt + (6 if herm else 5)) * (1 << N) * (1 << nt)

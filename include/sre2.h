@@ -68,7 +68,7 @@ extern "C" {
 /* ---- arithmetic forms -------------------------------------------------- */
 /* FP32: f_x and every butterfly in float32; |W|^2 in float32, squared and
  * accumulated in float64 (complex128 input is rounded to complex64 first).
- * For 11 <= N <= 16 (FP64: 15) the shifts x >= 1 run on chip as the
+ * For 10 <= N <= 16 (FP64: 15) the shifts x >= 1 run on chip as the
  * half transforms described at the Hermitian-pair forms below. */
 #define SRE2_FORM_FP32 0
 /* SPLIT_F16: the FP32 form with every group of four butterfly stages replaced

@@ -4,11 +4,11 @@
 //
 // Launch sequence of sre2_m2 on the caller's stream:
 //   [k_convert]        input -> working precision copy (only if dtype != form's)
-//   k_norm_part        FP64 partial norms + non-finite flags
+//   [k_norm_part]      FP64 partial norms + non-finite flags
 //   shift sums         k_tiny | k_fused | k_half | per chunk: k_pass1, k_pass2,
 //                      k_group_sum
-//   k_sum_part         fixed-range FP64 partial sums of S_x
-//   k_final            S, n, M2 = -log2(S / (2^N n^4)), status
+//   k_finish           sum of S_x, n, M2 = -log2(S / (2^N n^4)), status (N <= 14)
+//   or k_sum_part, k_final   fixed-range FP64 partial sums of S_x, then these
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -21,6 +21,7 @@
 #include "../../include/sre2.h"
 #include "sre2_internal.h"
 #include "sre2_ctx.h"
+#include "sre2_finish.h"
 
 using namespace sre2;
 
@@ -423,8 +424,14 @@ int m2_launch(sre2_ctx* tctx, const Workspace& ws, const void* psi, int N, int d
     const int64_t n = int64_t(1) << N;
     const Red r = red_of(ws.red);
     const int nb = red_blocks(n);
-    rc = norm_stage(tctx, work, N, form, r, nb, st);
-    if (rc) return rc;
+    // small N: the norm comes with the sum of S_x at the end, unless the
+    // transforms need it (scale of the split forms, bins of the histogram)
+    const bool finish = N <= kFinishMaxN;
+    const bool hist = spec && spec->kind == kRedHist;
+    if (!finish || (is_split(form) && !sx_given) || hist) {
+        rc = norm_stage(tctx, work, N, form, r, nb, st);
+        if (rc) return rc;
+    }
     double* Sx = partials ? partials : ws.sx;
     Spec sp{};
     if (spec) {
@@ -441,6 +448,13 @@ int m2_launch(sre2_ctx* tctx, const Workspace& ws, const void* psi, int N, int d
         rc = shift_sums(tctx, ws, work, N, form, 0, n, Sx, r.se, spec ? &sp : nullptr, st);
         if (rc) return rc;
     }
+    const int kind = spec ? sp.kind : kRedQuartic;
+    const double alpha = spec ? sp.alpha : 2.0;
+    if (finish) {
+        Timed tm(tctx, st, SRE2_KIND_AUX);
+        return hip_status(
+            launch_finish(work, work_dtype(form), Sx, N, out, Pack{}, kind, alpha, st));
+    }
     {
         Timed tm(tctx, st, SRE2_KIND_AUX);
         rc = hip_status(launch_sum(Sx, n, 1, nb, r.spart, nullptr, Pack{}, st));
@@ -448,7 +462,7 @@ int m2_launch(sre2_ctx* tctx, const Workspace& ws, const void* psi, int N, int d
     if (rc) return rc;
     Timed tm(tctx, st, SRE2_KIND_AUX);
     return hip_status(launch_final(r.spart, nb, r.npart, r.nflag, nb, N, out, Pack{},
-                                   spec ? sp.kind : kRedQuartic, spec ? sp.alpha : 2.0, st));
+                                   kind, alpha, st));
 }
 
 // Grow the context's input copy and reduction buffers (and S_x when the
@@ -517,10 +531,11 @@ int m2_pack(sre2_ctx* ctx, const void* const* psi, int count, int N, int dtype, 
     const bool half = half_path(N, form, nullptr);
     const bool herm = is_herm(form) && N >= herm_min(form);
     const int nb = red_blocks(n);
-    {
+    if (sp) {  // the split forms' scale
         Timed tm(ctx, st, SRE2_KIND_AUX);
-        if (launch_norm(nullptr, wd, n, nb, nullptr, nullptr, pk, st) != hipSuccess) return SRE2_EHIP;
-        if (sp && launch_split_scale(nullptr, nb, nullptr, pk, st) != hipSuccess) return SRE2_EHIP;
+        if (launch_norm(nullptr, wd, n, nb, nullptr, nullptr, pk, st) != hipSuccess ||
+            launch_split_scale(nullptr, nb, nullptr, pk, st) != hipSuccess)
+            return SRE2_EHIP;
     }
     if (fault_injected("launch")) return SRE2_EHIP;
     {
@@ -541,11 +556,7 @@ int m2_pack(sre2_ctx* ctx, const void* const* psi, int count, int N, int dtype, 
         if (e != hipSuccess) return SRE2_EHIP;
     }
     Timed tm(ctx, st, SRE2_KIND_AUX);
-    if (launch_sum(nullptr, n, 1, nb, nullptr, nullptr, pk, st) != hipSuccess) return SRE2_EHIP;
-    if (launch_final(nullptr, nb, nullptr, nullptr, nb, N, nullptr, pk, kRedQuartic, 2.0, st) !=
-        hipSuccess)
-        return SRE2_EHIP;
-    return SRE2_OK;
+    return hip_status(launch_finish(nullptr, wd, nullptr, N, nullptr, pk, kRedQuartic, 2.0, st));
 }
 
 }  // namespace

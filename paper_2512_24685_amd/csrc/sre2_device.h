@@ -299,6 +299,30 @@ __device__ __forceinline__ void lds_get(const C* lds, C (&v)[NV]) {
         v[OFF + i] = *lds_slot<SB, PADDED>(const_cast<C*>(lds), pb, pdep((uint32_t)i, REG));
 }
 
+// Sum over the 64 lanes of a wave: DPP exchanges inside each row of 16 lanes
+// (XOR partners 1, 2, 7, 15: every lane ends with the row's sum), then the
+// four rows in order.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double read_lane(double v, int l) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+    return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
+}
+
 // Sum over a block of NT threads (NT a multiple of 64): a butterfly of
 // cross-lane exchanges inside each wave (XOR partners 32, 16, ..., 1, so every
 // lane ends with the same wave sum), then the wave sums, added in wave order

@@ -62,7 +62,7 @@ __host__ __device__ constexpr bool fused_keeps_psi(int NT, bool herm) {
 
 // ---------------------------------------------------------------------------
 // Fused: whole transforms of NT bits in a 2^TB tile of SPT = 2^(TB-NT) shifts.
-// From N = 11 on only the split forms take it (and the FP32 spectrum of N = 11): the
+// From N = 10 on only the split forms take it (and the FP32 spectrum up to 11): the
 // half transforms of k_half do half the work and hold twice the waves (N = 14
 // FP32 450 -> 147 us, N = 13 FP64 142 -> 90 us per evaluation).
 //  HERM = false: NT = N, the tile element (slot j, k) is f_x(k), x = x0 + j.

@@ -73,14 +73,15 @@ constexpr int kMaxNAll = 26;
 #endif
 
 // On-chip half transforms (k_half): N from HMIN to HMAX.  HMIN: one wave holds
-// 2^(N-1) values (below it launches dominate and several shifts share a tile).
+// 2^(N-1) values, eight per lane (below it launches dominate and several
+// shifts share a tile).
 // HMAX: the half transform fills the register file of a CU (1024 threads of
 // 64 or 512 of 128 value registers) and its real parts 128 KiB of LDS.
 #ifndef SRE2_F32_HALF_MIN
-#define SRE2_F32_HALF_MIN 11
+#define SRE2_F32_HALF_MIN 10
 #endif
 #ifndef SRE2_F64_HALF_MIN
-#define SRE2_F64_HALF_MIN 11
+#define SRE2_F64_HALF_MIN 10
 #endif
 #ifndef SRE2_F32_HALF_MAX
 #define SRE2_F32_HALF_MAX 16
@@ -173,7 +174,8 @@ constexpr int fused_rb(int N, bool split) {
                 ? (sizeof(Real) == 4 ? SRE2_F32_FUSED_HALF_RB : SRE2_F64_FUSED_HALF_RB)
                 : 0);
 }
-// Registers (log2 of complex values) per thread of a half transform.  FP32: 16
+// Registers (log2 of complex values) per thread of a half transform: eight at
+// N = 10 (a whole wave; a pack of ten states 24 -> 12 us).  FP32: 16
 // values up to N = 13 (N = 12 12.9 against 14.1 us with 32, N = 13 44 against
 // 48), 32 above, which saves a round (N = 14 163 against 174 us); 32 for the
 // histogram, whose stage order is that of the plain 32-value tiles.  FP64: 16
@@ -182,13 +184,15 @@ constexpr int fused_rb(int N, bool split) {
 // against 306 us, N = 15 1.55 against 1.76 ms).
 template <typename Real>
 constexpr int half_rb(int N, bool hist) {
-    return N <= 13 && !(hist && sizeof(Real) == 4) ? 4 : 5;
+    if (hist && sizeof(Real) == 4) return 5;
+    return N <= 10 ? 3 : (N <= 13 ? 4 : 5);
 }
 // Smallest N whose histogram they take (a whole wave of threads).
 template <typename Real>
 constexpr int half_hist_min() {
-    return half_rb<Real>(Tune<Real>::HMIN, true) + 6 > Tune<Real>::HMIN - 1 ? Tune<Real>::HMIN + 1
-                                                                            : Tune<Real>::HMIN;
+    int N = Tune<Real>::HMIN;
+    while (half_rb<Real>(N, true) + 6 > N - 1) ++N;
+    return N;
 }
 // Largest N whose histogram the half transforms take: the FP32 counts depend
 // on every rounding, so there the order of stages has to be the plain

@@ -1,4 +1,4 @@
-// sre2_half.hip - on-chip half transforms: S_x of whole shifts, 11 <= N <= 16
+// sre2_half.hip - on-chip half transforms: S_x of whole shifts, 10 <= N <= 16
 // (FP32) / 15 (FP64), for every form but the split ones.
 //
 // For x != 0, f_x(k ^ x) = conj f_x(k) (the summand of Eq. 3 at k and k ^ x),
@@ -100,30 +100,6 @@ struct HalfRunner {
     }
 };
 
-// Sum over the 64 lanes of a wave: DPP exchanges inside each row of 16 lanes
-// (XOR partners 1, 2, 7, 15: every lane ends with the row's sum), then the
-// four rows in order.
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double read_lane(double v, int l) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double wave_sum(double v) {
-    v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-    v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-    v = dpp_add<0x141>(v);  // row_half_mirror
-    v = dpp_add<0x140>(v);  // row_mirror
-    return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
-}
-
 // Waves per SIMD asked of the compiler: with 64 registers of values per thread
 // four fit (128 registers each), with 128 (FP64 N = 14, 15) two.
 // (The histogram's terms spill a few words at four; three waves without spills
@@ -167,8 +143,9 @@ __host__ __device__ constexpr BitOrder zero_map() {
 }
 
 // Blocks of a histogram launch: each adds its bins to the global counters once
-// (one block per shift would queue 2^N of them at the same few addresses).
-constexpr int kHistBlocks = 2048;
+// (one block per shift would queue 2^N of them at the same few addresses), and
+// takes four shifts or more.
+constexpr int64_t kHistBlocks = 2048;
 
 // Reductions: the sum of |W|^4, the general sums, the histogram.
 enum HalfRed { RED_QUARTIC, RED_GEN, RED_HIST };
@@ -322,7 +299,8 @@ hipError_t launch_half_n(const void* psi, int64_t x0, int64_t xc, double* S, con
                          const Spec& sp, int bit, hipStream_t st) {
     using C = typename CT<Real>::T;
     constexpr int RB = half_rb<Real>(N, RED == RED_HIST);
-    const int64_t blocks = RED == RED_HIST && xc > kHistBlocks ? kHistBlocks : xc;
+    const int64_t blocks =
+        RED != RED_HIST ? xc : ((xc + 3) / 4 < kHistBlocks ? (xc + 3) / 4 : kHistBlocks);
     hipLaunchKernelGGL((k_half<Real, N - 1, RB, RED>),
                        dim3((unsigned)blocks, (unsigned)(pk.count ? pk.count : 1)),
                        dim3(1 << (N - 1 - RB)), 0, st, (const C*)psi, x0, xc, S, pk, sp, bit);

@@ -24,7 +24,8 @@
 //                  2i Im of the result are the values of the shift.
 // Here:
 //  k_convert / k_norm_part / k_sum_part / k_final: input staging, FP64 norm,
-//              fixed-order FP64 reductions and the logarithm.
+//              fixed-order FP64 reductions and the logarithm (N above the
+//              range of k_finish, sre2_finish.h, which does the last three).
 //  k_moment_part / k_moment_final: sum |psi|^2, sum |psi|^4 and non-finite
 //              count of an input (sre2_moments).
 //
@@ -43,6 +44,7 @@
 
 #include "sre2_internal.h"
 #include "sre2_device.h"
+#include "sre2_finish.h"
 
 namespace sre2 {
 
@@ -138,14 +140,8 @@ __global__ __launch_bounds__(kRedThreads) void k_sum_part(const double* __restri
                                                           int64_t nshift, int P,
                                                           int64_t per_block,
                                                           double* __restrict__ part,
-                                                          double* __restrict__ Sx,
-                                                          const Pack pk) {
+                                                          double* __restrict__ Sx) {
     __shared__ double red[kRedThreads];
-    if (pk.count) {
-        v = pk_sx(pk.ws[blockIdx.y], pk.N);
-        part = pk_spart(pk.ws[blockIdx.y], pk.N);
-        Sx = nullptr;
-    }
     const int64_t lo = (int64_t)blockIdx.x * per_block;
     const int64_t hi = lo + per_block < nshift ? lo + per_block : nshift;
     double s = 0.0;
@@ -173,15 +169,9 @@ __global__ __launch_bounds__(256) void k_group_sum(const double* __restrict__ pa
 __global__ __launch_bounds__(kRedThreads) void k_final(const double* __restrict__ spart, int ns,
                                                        const double* __restrict__ npart,
                                                        const double* __restrict__ nflag, int nn,
-                                                       int N, double* __restrict__ out,
-                                                       const Pack pk, int kind, double alpha) {
+                                                       int N, double* __restrict__ out, int kind,
+                                                       double alpha) {
     __shared__ double red[kRedThreads];
-    if (pk.count) {
-        spart = pk_spart(pk.ws[blockIdx.y], pk.N);
-        npart = pk_npart(pk.ws[blockIdx.y], pk.N);
-        nflag = pk_nflag(pk.ws[blockIdx.y], pk.N);
-        out = pk.out[blockIdx.y];
-    }
     double a = 0.0, b = 0.0, c = 0.0;
     for (int i = threadIdx.x; i < ns; i += kRedThreads) a += spart[i];
     for (int i = threadIdx.x; i < nn; i += kRedThreads) {
@@ -191,21 +181,7 @@ __global__ __launch_bounds__(kRedThreads) void k_final(const double* __restrict_
     const double S = block_sum<kRedThreads>(a, red);
     const double n = block_sum<kRedThreads>(b, red);
     const double bad = block_sum<kRedThreads>(c, red);
-    if (threadIdx.x == 0) {
-        const bool ok = bad == 0.0 && n > 0.0 && isfinite(n) && isfinite(S);
-        const double n2 = n * n;
-        double m = NAN;
-        if (kind == kRedQuartic)
-            m = -log2(S / (ldexp(1.0, N) * n2 * n2));
-        else if (kind == kRedPow)  // Eq. 1: log2(S / (2^N n^(2 alpha))) / (1 - alpha)
-            m = (log2(S) - (double)N - alpha * log2(n2)) / (1.0 - alpha);
-        else if (kind == kRedShannon)  // alpha -> 1, with sum_P w = 2^N n^2
-            m = log2(n2) - S / (ldexp(1.0, N) * n2);
-        out[0] = ok ? m : NAN;
-        out[1] = S;
-        out[2] = n;
-        out[3] = ok ? 0.0 : 1.0;
-    }
+    if (threadIdx.x == 0) final_out(S, n, bad, N, kind, alpha, out);
 }
 
 // s = 14 - ceil(log2 n) from the norm partials (0 when n is not positive and
@@ -279,9 +255,10 @@ hipError_t launch_moments(const void* psi, int dtype, int64_t n, int nblocks, do
 
 hipError_t launch_sum(const double* v, int64_t nshift, int P, int nblocks, double* part,
                       double* Sx, const Pack& pk, hipStream_t st) {
+    if (pk.count) return hipErrorInvalidValue;  // packed sizes: finish (sre2_finish.h)
     const int64_t per = (nshift + nblocks - 1) / nblocks;
-    hipLaunchKernelGGL(k_sum_part, dim3(nblocks, pk.count ? pk.count : 1), dim3(kRedThreads), 0, st, v, nshift, P,
-                       per, part, Sx, pk);
+    hipLaunchKernelGGL(k_sum_part, dim3(nblocks), dim3(kRedThreads), 0, st, v, nshift, P, per,
+                       part, Sx);
     return hipGetLastError();
 }
 
@@ -294,8 +271,9 @@ hipError_t launch_group_sum(const double* part, int64_t ns, int P, double* Sx, h
 hipError_t launch_final(const double* spart, int ns, const double* npart, const double* nflag,
                         int nn, int N, double* out, const Pack& pk, int kind, double alpha,
                         hipStream_t st) {
-    hipLaunchKernelGGL(k_final, dim3(1, pk.count ? pk.count : 1), dim3(kRedThreads), 0, st, spart, ns, npart, nflag,
-                       nn, N, out, pk, kind, alpha);
+    if (pk.count) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, st, spart, ns, npart, nflag, nn, N,
+                       out, kind, alpha);
     return hipGetLastError();
 }
 

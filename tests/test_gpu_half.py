@@ -30,8 +30,8 @@ def _gpu():
         pytest.skip("no GPU")
 
 
-@pytest.mark.parametrize("form,N", [("fp32", 12), ("fp32", 14), ("fp32", 15), ("fp32", 16),
-                                    ("fp32h", 16), ("fp64", 11), ("fp64", 13), ("fp64", 14),
+@pytest.mark.parametrize("form,N", [("fp32", 10), ("fp32", 11), ("fp32", 12), ("fp32", 14),
+                                    ("fp32", 15), ("fp32", 16), ("fp32h", 16), ("fp64", 10), ("fp64", 11), ("fp64", 13), ("fp64", 14),
                                     ("fp64h", 15)])
 def test_range_edges(oracle_mod, form, N):
     c128 = form.startswith("fp64")
@@ -59,14 +59,20 @@ def test_general_index(oracle_mod, form, N, alpha):
     assert r.status == 0 and abs(r.m2 - ref) <= (1e-9 if c128 else 1e-5)
 
 
-@pytest.mark.parametrize("form,N", [("fp32", 12), ("fp32", 14), ("fp64", 11), ("fp64", 13)])
+@pytest.mark.parametrize("form,N", [("fp32", 5), ("fp32", 10), ("fp32", 12), ("fp32", 14),
+                                    ("split16", 13), ("fp64", 11), ("fp64", 13)])
 def test_packed_states_equal_single_calls(form, N):
     c128 = form.startswith("fp64")
     psis = [dev(W.haar(N, 4300 + j, np.complex128 if c128 else np.complex64)) for j in range(3)]
     print("CASE half packed", form, N, flush=True)
     for p, b in zip(psis, sre2.m2_batched(psis, form=form)):
-        a = sre2.m2(p, form=form)
+        a = sre2.m2(p, form=form, partials=True)
         assert a.m2 == b.m2 and a.S == b.S and b.status == 0
+        # the end of the evaluation: sum of S_x and the norm, in FP64
+        assert abs(a.S - a.partials.sum().item()) <= 1e-14 * a.S
+        assert abs(a.n - 1.0) <= (1e-13 if c128 else 1e-6)
+        c = sre2.m2_from_partials(p, a.partials, form=form)
+        assert a.m2 == c.m2 and a.n == c.n
 
 
 @pytest.mark.parametrize("form,N", [("fp32", 12), ("fp32", 14), ("fp32", 15), ("fp32", 17),
