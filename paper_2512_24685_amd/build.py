@@ -19,8 +19,8 @@ PROBE = os.path.join(HERE, "probe_mall")  # memory-hierarchy probe (bench.py --m
 PROBE_LDS = os.path.join(HERE, "probe_lds")  # LDS bank-conflict probe (run under rocprofv3)
 PROBE_STORE = os.path.join(HERE, "probe_store")  # HBM store-rate probe of slab layouts
 SOURCES = ["sre2_fused.hip", "sre2_half.hip", "sre2_pass1.hip", "sre2_pass2.hip",
-           "sre2_kernels.hip", "sre2_api.hip", "sre2_server.hip", "sre2_sim.hip",
-           "sre2_noalloc.hip", "sre2_queries.hip"]
+           "sre2_pass2_images.hip", "sre2_kernels.hip", "sre2_api.hip", "sre2_server.hip",
+           "sre2_sim.hip", "sre2_noalloc.hip", "sre2_queries.hip"]
 ARCH = "gfx950"
 
 HIP_FLAGS = [

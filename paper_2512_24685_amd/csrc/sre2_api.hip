@@ -97,15 +97,18 @@ int row_bits(int form, int NS) {
     return is_f64(form) ? pass1_row_bits<double>(NS) : pass1_row_bits<float>(NS);
 }
 int herm_min(int form) { return is_f64(form) ? herm_min_n<double>() : herm_min_n<float>(); }
-// The half transforms take this evaluation (spec: its reduction, null for M2).
+// The half transforms take this evaluation (spec: its reduction, null for M2);
+// the split forms' shift 0 goes through their other kernels.
 bool half_path(int N, int form, const Spec* spec) {
     const bool hist = spec && spec->kind == kRedHist;
-    return !is_split(form) &&
-           (is_f64(form) ? half_takes<double>(N, hist) : half_takes<float>(N, hist));
+    return is_f64(form) ? half_takes<double>(N, hist, false)
+                        : half_takes<float>(N, hist, split_kind(form));
 }
-// The evaluation goes through the two-pass kernels.
-bool two_pass_path(int N, int form, const Spec* spec) {
-    return N > fused_max(form) && !half_path(N, form, spec);
+// Shifts of [x0, x0 + xc) that go through the two-pass kernels (from x0 on).
+int64_t two_pass_shifts(int N, int form, const Spec* spec, int64_t x0, int64_t xc) {
+    if (N <= fused_max(form)) return 0;
+    if (half_path(N, form, spec)) return is_split(form) && x0 == 0 ? 1 : 0;
+    return xc;
 }
 int64_t col_tiles(int N, int form, int slab) {
     return is_f64(form) ? pass2_col_tiles<double>(N, slab) : pass2_col_tiles<float>(N, slab);
@@ -119,7 +122,7 @@ struct Chunking {
 
 // Slab bits of one shift and pass-1 row bits of a slab kind.
 int slab_bits(int N, int slab) {
-    return N - (slab == kSlabHerm || slab == kSlabPairs ? 1 : 0);
+    return N - (slab == kSlabHerm || slab == kSlabPairs || slab == kSlabImages ? 1 : 0);
 }
 int slab_rows(int form, int N, int slab) {
     return row_bits(form, slab == kSlabHerm ? N - 1 : N);
@@ -158,6 +161,7 @@ int high_slab(int N, int form, bool pairs, const Spec* spec) {
     if (spec && spec->kind == kRedHist && !is_f64(form) &&
         N - slab_rows(form, N, kSlabFull) > pass2_round_bits<float>())
         return kSlabFull;
+    if (pairs && split_kind(form) == 2 && N <= kImagesMaxN) return kSlabImages;
     if (pairs) return kSlabPairs;
     return spec || is_split(form) ? kSlabFull : kSlabBoth;
 }
@@ -330,7 +334,8 @@ int ctx_two_pass_ws(sre2_ctx* ctx, int N, int form, int64_t x0, int64_t xc, cons
                     Workspace* ws) {
     ws->pairs = ctx->row_pairs;
     const int high = high_slab(N, form, ws->pairs, spec);
-    if (!two_pass_path(N, form, spec)) return SRE2_OK;
+    xc = two_pass_shifts(N, form, spec, x0, xc);
+    if (xc == 0) return SRE2_OK;
     size_t limit = ctx->scratch_limit, need = 0, need_part = 0;
     int rc;
     for (;;) {
@@ -358,12 +363,24 @@ int shift_sums(sre2_ctx* tctx, const Workspace& ws, const void* work, int N, int
     const bool f64 = is_f64(form);
     const int sp = split_kind(form);
     if (half_path(N, form, spec)) {
+        // the split forms' shift 0 first
+        const int64_t first = sp && x0 == 0 ? 1 : 0;
+        int rc = SRE2_OK;
+        if (first && N > fused_max(form)) {
+            rc = two_pass(tctx, ws, work, N, form, kSlabFull, 0, 1, Sx, se, spec, st);
+        } else if (first) {
+            Timed tm(tctx, st, SRE2_KIND_SHIFT);
+            rc = hip_status(launch_shift_kernel<float>(work, N, false, sp, 0, 1, Sx, se, Pack{},
+                                                       spec, st));
+        }
+        if (rc || xc == first) return rc;
         Timed tm(tctx, st, SRE2_KIND_SHIFT);
         const bool herm = is_herm(form);
         return hip_status(f64 ? launch_shift_kernel<double>(work, N, herm, 0, x0, xc, Sx, se,
                                                             Pack{}, spec, st)
-                              : launch_shift_kernel<float>(work, N, herm, 0, x0, xc, Sx, se,
-                                                           Pack{}, spec, st));
+                              : launch_shift_kernel<float>(work, N, herm, sp, x0 + first,
+                                                           xc - first, Sx + first, se, Pack{},
+                                                           spec, st));
     }
     const int64_t x1 = x0 + xc;
     if (N <= fused_max(form)) {
@@ -540,18 +557,20 @@ int m2_pack(sre2_ctx* ctx, const void* const* psi, int count, int N, int dtype, 
     if (fault_injected("launch")) return SRE2_EHIP;
     {
         Timed tm(ctx, st, SRE2_KIND_SHIFT);
-        // the half transforms take every shift of a packed size, 0 included
-        const int64_t plain_end = herm ? 1 : n;
-        hipError_t e = f64 ? launch_shift_kernel<double>(nullptr, N, false, false, 0,
-                                                         half ? n : plain_end, nullptr, nullptr,
-                                                         pk, nullptr, st)
-                           : launch_shift_kernel<float>(nullptr, N, false, sp, 0,
-                                                        half ? n : plain_end, nullptr, nullptr,
-                                                        pk, nullptr, st);
-        if (e == hipSuccess && herm && !half)
-            e = f64 ? launch_shift_kernel<double>(nullptr, N, true, false, 1, n - 1, nullptr,
+        // shift 0 on its own: Hermitian-pair forms below the half transforms,
+        // split forms on them
+        const int64_t first = half ? (sp ? 1 : 0) : (herm ? 1 : 0);
+        hipError_t e = hipSuccess;
+        if (first)
+            e = f64 ? launch_shift_kernel<double>(nullptr, N, false, 0, 0, 1, nullptr, nullptr, pk,
+                                                  nullptr, st)
+                    : launch_shift_kernel<float>(nullptr, N, false, sp, 0, 1, nullptr, nullptr, pk,
+                                                 nullptr, st);
+        const bool pair = herm && !half;
+        if (e == hipSuccess)
+            e = f64 ? launch_shift_kernel<double>(nullptr, N, pair, 0, first, n - first, nullptr,
                                                   nullptr, pk, nullptr, st)
-                    : launch_shift_kernel<float>(nullptr, N, true, false, 1, n - 1, nullptr,
+                    : launch_shift_kernel<float>(nullptr, N, pair, sp, first, n - first, nullptr,
                                                  nullptr, pk, nullptr, st);
         if (e != hipSuccess) return SRE2_EHIP;
     }
@@ -582,11 +601,12 @@ int ws_layout(int N, int dtype, int form, bool need_sx, size_t bytes, size_t* ps
         off = up(off + n * sizeof(double));
     }
     if (off > bytes) return SRE2_ESCRATCH;
-    if (!two_pass_path(N, form, nullptr)) return SRE2_OK;
+    const int64_t xc = two_pass_shifts(N, form, nullptr, 0, (int64_t)n);
+    if (xc == 0) return SRE2_OK;
     // the largest chunks whose slab and partials fit what is left
     size_t lim = bytes - off, need = 0, need_part = 0;
     for (;;) {
-        const int64_t cs = slab_need(N, form, high_slab(N, form, true, nullptr), 0, (int64_t)n, lim,
+        const int64_t cs = slab_need(N, form, high_slab(N, form, true, nullptr), 0, xc, lim,
                                       &need, &need_part);
         const size_t pb = up(need_part * sizeof(double));
         if (off + pb + need <= bytes) {

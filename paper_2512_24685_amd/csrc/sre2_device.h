@@ -216,9 +216,13 @@ __device__ __forceinline__ uint32_t insert0(uint32_t v, uint32_t hb) {
 }
 
 // Row bit left out of a half slab (Hermitian pair, row pairs), for the row
-// part xh = x >> L (nonzero) of a shift x: the top set bit of xh.  Pass 1
-// then builds only the slab rows with that bit clear.
-__device__ __forceinline__ int half_row_bit(uint32_t xh) { return 31 - __builtin_clz(xh); }
+// part xh = x >> L (nonzero) of a shift x: the lowest set bit inside `pref`
+// when there is one (the rebuilt rows of launch_pass2_images), else the top
+// set bit.  Pass 1 then builds only the slab rows with that bit clear.
+__device__ __forceinline__ int half_row_bit(uint32_t xh, uint32_t pref) {
+    const uint32_t p = xh & pref;
+    return p ? __builtin_ctz(p) : 31 - __builtin_clz(xh);
+}
 
 // Butterflies over the register bits of `bfly` (a subset of `reg`), one tile
 // bit at a time (compile-time recursion keeps every register index constant).

@@ -315,8 +315,10 @@ hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int
                                int64_t xc, double* S, const int* se, const Pack& pk,
                                const Spec* sp, hipStream_t st) {
     const bool hist = sp && sp->kind == kRedHist;
-    const bool half = !split && (hist ? N >= half_hist_min<Real>() && N <= half_hist_max<Real>()
-                                      : N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX);
+    // (the split forms' shift 0 goes through k_fused)
+    const bool half = split  ? split == 1 && x0 > 0 && N >= Tune<Real>::HSPLIT && N <= Tune<Real>::HMAX
+                      : hist ? N >= half_hist_min<Real>() && N <= half_hist_max<Real>()
+                             : N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX;
     if ((N > Tune<Real>::FMAX && !half) || split < 0 || split > 2 ||
         (split && (herm || sizeof(Real) != 4)) || pk.count > kMaxPack)
         return hipErrorInvalidValue;
@@ -325,7 +327,7 @@ hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int
             (hist && (!sp->hist || !sp->nrm || sp->nbins < 2 || sp->nbins > kMaxBins)))
             return hipErrorInvalidValue;
     }
-    if (half) return launch_half<Real>(psi, N, herm, x0, xc, S, pk, sp, st);
+    if (half) return launch_half<Real>(psi, N, herm, split, x0, xc, S, se, pk, sp, st);
     if (sp)
         return shift_kernel_gen<Real, true>(psi, N, herm, split, x0, xc, S, se, pk, *sp, st);
     return shift_kernel_gen<Real, false>(psi, N, herm, split, x0, xc, S, se, pk, Spec{}, st);

@@ -83,6 +83,9 @@ constexpr int kMaxNAll = 26;
 #ifndef SRE2_F64_HALF_MIN
 #define SRE2_F64_HALF_MIN 10
 #endif
+#ifndef SRE2_SPLIT_HALF_MIN
+#define SRE2_SPLIT_HALF_MIN 13  // the split forms; below, shift 0's own launch costs as much
+#endif
 #ifndef SRE2_F32_HALF_MAX
 #define SRE2_F32_HALF_MAX 16
 #endif
@@ -97,6 +100,7 @@ template <> struct Tune<float> {
     static constexpr int RB1 = SRE2_F32_RB1, RB2 = SRE2_F32_RB2, P2MIN = SRE2_F32_P2_MIN;
     static constexpr int P2COLS = SRE2_F32_P2_COLS;
     static constexpr int HMIN = SRE2_F32_HALF_MIN, HMAX = SRE2_F32_HALF_MAX;
+    static constexpr int HSPLIT = SRE2_SPLIT_HALF_MIN;
 };
 template <> struct Tune<double> {
     static constexpr int RBF = SRE2_F64_RB_FUSED, FMIN = SRE2_F64_FUSED_MIN;
@@ -104,6 +108,7 @@ template <> struct Tune<double> {
     static constexpr int RB1 = SRE2_F64_RB1, RB2 = SRE2_F64_RB2, P2MIN = SRE2_F64_P2_MIN;
     static constexpr int P2COLS = SRE2_F64_P2_COLS;
     static constexpr int HMIN = SRE2_F64_HALF_MIN, HMAX = SRE2_F64_HALF_MAX;
+    static constexpr int HSPLIT = SRE2_SPLIT_HALF_MIN;
 };
 
 // Row bits of pass 1 for a slab of NS bits (NS = N, or N - 1 in the
@@ -183,8 +188,8 @@ constexpr int fused_rb(int N, bool split) {
 // a round where the LDS leaves two or one workgroup per CU anyway (N = 14 283
 // against 306 us, N = 15 1.55 against 1.76 ms).
 template <typename Real>
-constexpr int half_rb(int N, bool hist) {
-    if (hist && sizeof(Real) == 4) return 5;
+constexpr int half_rb(int N, bool five) {  // five: the FP32 histogram, the split forms
+    if (five && sizeof(Real) == 4) return 5;
     return N <= 10 ? 3 : (N <= 13 ? 4 : 5);
 }
 // Smallest N whose histogram they take (a whole wave of threads).

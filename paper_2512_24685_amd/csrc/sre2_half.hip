@@ -1,5 +1,5 @@
 // sre2_half.hip - on-chip half transforms: S_x of whole shifts, 10 <= N <= 16
-// (FP32) / 15 (FP64), for every form but the split ones.
+// (FP32) / 15 (FP64), for every form but the BF16 split one (FP16: from 13 on).
 //
 // For x != 0, f_x(k ^ x) = conj f_x(k) (the summand of Eq. 3 at k and k ^ x),
 // so with hb a set bit of x the transform A of f_x over the half space
@@ -20,7 +20,7 @@
 // it replaces: 450 us); the same buffer lets N = 15 and 16 (FP64: 14 and 15)
 // stay on chip at all, where the two passes through HBM moved 8 (16) bytes
 // per Pauli string (N = 16 FP32: 6.9 ms before, 4.2 ms here; FP64 N = 15:
-// 5.0 ms before, 1.55 ms).  The bound is the VALU: N - 1 additions, the
+// 3.2 ms before, 1.55 ms).  The bound is the VALU: N - 1 additions, the
 // product (2) and the term (3) per Pauli string, 0.13 ms at N = 14.
 //
 // Measured and not taken (N = 14 FP32): keeping psi[k] and psi[k ^ x] in
@@ -34,10 +34,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "sre2_plan.h"
-#include "sre2_geometry.h"
-#include "sre2_internal.h"
-#include "sre2_device.h"
+#include "sre2_tile.h"
 
 namespace sre2 {
 
@@ -76,13 +73,25 @@ __device__ __forceinline__ void lds_part(Real* lds, C (&v)[1 << RB]) {
     }
 }
 
-// Rounds J .. nrounds - 1 of the half transform of NT bits.
-template <typename Real, int NT, int RB, int J>
+// Plan of the half transform of NT bits (split form s: H_16 factors on the
+// matrix cores, as in the other kernels of the split forms).
+template <int NT, int RB, int SPLIT>
+__host__ __device__ constexpr Plan half_plan() {
+    return SPLIT ? make_split_plan(NT, RB, 5, 0, NT, 0) : make_plan(NT, RB, 5, 0, NT);
+}
+
+// Rounds J .. nrounds - 1 of the half transform.
+template <typename Real, int NT, int RB, int SPLIT, int J>
 struct HalfRunner {
     using C = typename CT<Real>::T;
-    static constexpr Plan P = make_plan(NT, RB, 5, 0, NT);
+    static constexpr Plan P = half_plan<NT, RB, SPLIT>();
     static constexpr int NV = P.nrounds < 2 ? 1 : (int)pad_rt((1u << NT) - 1u, 5) + 1;
-    __device__ __forceinline__ static void run(Real* lds, C (&v)[1 << RB]) {
+    __device__ __forceinline__ static void math(C (&v)[1 << RB], const op8 amat) {
+        constexpr Round c = P.r[J];
+        butterflies<RB, c.reg, c.bfly>(v);
+        if constexpr (c.mf != 0) mf_apply<SPLIT, RB, mf_reg_index(c)>(v, amat);
+    }
+    __device__ __forceinline__ static void run(Real* lds, C (&v)[1 << RB], const op8 amat) {
         if constexpr (J < P.nrounds) {
             constexpr Round a = P.r[J - 1];
             constexpr Round c = P.r[J];
@@ -94,8 +103,8 @@ struct HalfRunner {
             lds_part<true, 1, RB, a.reg, a.lperm, a.wave>(lds, v);
             __syncthreads();
             lds_part<false, 1, RB, c.reg, c.lperm, c.wave>(lds, v);
-            butterflies<RB, c.reg, c.bfly>(v);
-            HalfRunner<Real, NT, RB, J + 1>::run(lds, v);
+            math(v, amat);
+            HalfRunner<Real, NT, RB, SPLIT, J + 1>::run(lds, v, amat);
         }
     }
 };
@@ -131,7 +140,7 @@ __host__ __device__ constexpr BitOrder plain_order(int N) {
 // and imaginary part.
 template <typename Real, int NT, int RB>
 __host__ __device__ constexpr BitOrder zero_map() {
-    constexpr Plan P = HalfRunner<Real, NT, RB, 1>::P;
+    constexpr Plan P = half_plan<NT, RB, 0>();
     constexpr BitOrder o = plain_order<Real>(NT + 1);
     BitOrder m{};
     int n = 0;
@@ -161,13 +170,21 @@ enum HalfBit { HB_TOP, HB_LAST };
 
 // Block b of the grid takes shift x_begin + b, and with RED_HIST every
 // gridDim.x-th one from there (so that few blocks add to the global counters).
-template <typename Real, int NT, int RB, int RED>
+// SPLIT (1): shifts x >= 1 of the FP16 split form, values scaled by
+// 2^*scale_exp; N = 14 442 -> 156 us, N = 16 10.0 -> 4.3 ms.  Shift 0, whose W_0
+// is a quarter of S, keeps the order of its matrix products: the other kernels
+// of the form take it.  The BF16 form is not taken here: under another order its
+// 16-bit halves move the S_x of N = 13 to 16 by 2e-9 to 1.5e-8 (2-norm), FP16's
+// 22 bits by 4e-10 or less.
+template <typename Real, int NT, int RB, int RED, int SPLIT>
 __global__ __launch_bounds__(1 << (NT - RB))
 __attribute__((amdgpu_waves_per_eu(half_waves_per_simd<Real>(RB))))
 void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64_t x_count,
-            double* __restrict__ S_out, const Pack pk, const Spec sp, int bit) {
+            double* __restrict__ S_out, const int* __restrict__ scale_exp, const Pack pk,
+            const Spec sp, int bit) {
+    static_assert(!SPLIT || (RED == RED_QUARTIC && sizeof(Real) == 4), "split forms: M2 in FP32");
     using C = typename CT<Real>::T;
-    using HR = HalfRunner<Real, NT, RB, 1>;
+    using HR = HalfRunner<Real, NT, RB, SPLIT, 1>;
     constexpr int N = NT + 1;
     constexpr int NW = (1 << (NT - RB)) / 64;
     constexpr int NE = 1 << RB;
@@ -179,7 +196,11 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
     if (pk.count) {
         psi = (const C*)pk.psi[blockIdx.y];
         S_out = pk_sx(pk.ws[blockIdx.y], N) + x_begin;
+        scale_exp = pk_se(pk.ws[blockIdx.y], N);
     }
+    const int se = SPLIT ? *scale_exp : 0;
+    op8 amat = {};
+    if constexpr (SPLIT != 0) amat = h16_operand<SPLIT>();
     Real lnorm2 = Real(0);
     if constexpr (RED == RED_HIST) {
         hist_clear(lh, sp);
@@ -189,12 +210,12 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
     const uint32_t base = thread_base<r0.lperm, r0.wave>();
     const auto one_shift = [&](uint32_t at) {
         const uint32_t x = (uint32_t)x_begin + at;
-        const bool zero = x == 0;
+        const bool zero = SPLIT == 0 && x == 0;
         C v[NE];
         if (zero) {
             // a rolled loop through the thread's own LDS slots, so that one
             // workgroup's case does not cost the others registers
-            static_assert(r0.reg == top_bits(bits_range(0, NT), RB), "element bits of a register");
+            static_assert(SPLIT || r0.reg == top_bits(bits_range(0, NT), RB), "element bits");
             constexpr BitOrder map = zero_map<Real, NT, RB>();
             const auto squares = [&](uint32_t half) {
 #pragma unroll 1
@@ -244,9 +265,17 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
                 else
                     v[i] = cmul_conj_f(load_at<C>(rs, vb, kr ^ xr), load_at<C>(rs, kb, kr));
             }
+            if constexpr (SPLIT != 0) {
+                const Real sc = ldexpf(1.0f, se);
+#pragma unroll
+                for (int i = 0; i < NE; ++i) {
+                    v[i].x *= sc;
+                    v[i].y *= sc;
+                }
+            }
         }
-        butterflies<RB, r0.reg, r0.bfly>(v);
-        HR::run(lds, v);
+        HalfRunner<Real, NT, RB, SPLIT, 0>::math(v, amat);
+        HR::run(lds, v, amat);
         double acc = 0.0;
         if (zero) {
             // the last stage, across the two halves: two values of W, halved
@@ -261,7 +290,7 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
         if constexpr (RED == RED_QUARTIC) {
 #pragma unroll
             for (int i = 0; i < NE; ++i) acc += abs4h(v[i]);
-            acc *= 16.0;
+            acc *= SPLIT ? ldexp(16.0, -4 * se) : 16.0;
         } else {
             acc = gen_sum<Real, GEN_HERM, RED == RED_HIST>(v, sp, lnorm2, lh);
         }
@@ -294,27 +323,29 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
     }
 }
 
-template <typename Real, int N, int RED>
-hipError_t launch_half_n(const void* psi, int64_t x0, int64_t xc, double* S, const Pack& pk,
-                         const Spec& sp, int bit, hipStream_t st) {
+template <typename Real, int N, int RED, int SPLIT>
+hipError_t launch_half_n(const void* psi, int64_t x0, int64_t xc, double* S, const int* se,
+                         const Pack& pk, const Spec& sp, int bit, hipStream_t st) {
     using C = typename CT<Real>::T;
-    constexpr int RB = half_rb<Real>(N, RED == RED_HIST);
+    constexpr int RB = half_rb<Real>(N, RED == RED_HIST || SPLIT);
     const int64_t blocks =
         RED != RED_HIST ? xc : ((xc + 3) / 4 < kHistBlocks ? (xc + 3) / 4 : kHistBlocks);
-    hipLaunchKernelGGL((k_half<Real, N - 1, RB, RED>),
+    hipLaunchKernelGGL((k_half<Real, N - 1, RB, RED, SPLIT>),
                        dim3((unsigned)blocks, (unsigned)(pk.count ? pk.count : 1)),
-                       dim3(1 << (N - 1 - RB)), 0, st, (const C*)psi, x0, xc, S, pk, sp, bit);
+                       dim3(1 << (N - 1 - RB)), 0, st, (const C*)psi, x0, xc, S, se, pk, sp, bit);
     return hipGetLastError();
 }
 
-template <typename Real, int RED, int... Ns>
-hipError_t dispatch_half(int N, const void* psi, int64_t x0, int64_t xc, double* S,
+template <typename Real, int RED, int SPLIT, int... Ns>
+hipError_t dispatch_half(int N, const void* psi, int64_t x0, int64_t xc, double* S, const int* se,
                          const Pack& pk, const Spec& sp, int bit, hipStream_t st,
                          std::integer_sequence<int, Ns...>) {
     hipError_t e = hipErrorInvalidValue;
-    constexpr int N0 = RED == RED_HIST ? half_hist_min<Real>() : Tune<Real>::HMIN;
+    constexpr int N0 = SPLIT             ? Tune<Real>::HSPLIT
+                       : RED == RED_HIST ? half_hist_min<Real>()
+                                         : Tune<Real>::HMIN;
     ((N == Ns + N0
-          ? (e = launch_half_n<Real, Ns + N0, RED>(psi, x0, xc, S, pk, sp, bit, st), 0)
+          ? (e = launch_half_n<Real, Ns + N0, RED, SPLIT>(psi, x0, xc, S, se, pk, sp, bit, st), 0)
           : 0),
      ...);
     return e;
@@ -323,23 +354,33 @@ hipError_t dispatch_half(int N, const void* psi, int64_t x0, int64_t xc, double*
 }  // namespace
 
 template <typename Real>
-hipError_t launch_half(const void* psi, int N, bool herm, int64_t x0, int64_t xc, double* S,
-                       const Pack& pk, const Spec* sp, hipStream_t st) {
+hipError_t launch_half(const void* psi, int N, bool herm, int split, int64_t x0, int64_t xc,
+                       double* S, const int* se, const Pack& pk, const Spec* sp, hipStream_t st) {
+    using T = Tune<Real>;
     const bool hist = sp && sp->kind == kRedHist;
-    if (xc < 1 || x0 < 0 || x0 + xc > ((int64_t)1 << N))
-        return hipErrorInvalidValue;
-    constexpr auto ns = std::make_integer_sequence<int, Tune<Real>::HMAX - Tune<Real>::HMIN + 1>{};
+    if (xc < 1 || x0 < (split ? 1 : 0) || x0 + xc > ((int64_t)1 << N)) return hipErrorInvalidValue;
+    constexpr auto ns = std::make_integer_sequence<int, T::HMAX - T::HMIN + 1>{};
     constexpr auto hs =
         std::make_integer_sequence<int, half_hist_max<Real>() - half_hist_min<Real>() + 1>{};
+    const Spec none{};
+    if constexpr (sizeof(Real) == 4) {
+        constexpr auto ss = std::make_integer_sequence<int, T::HMAX - T::HSPLIT + 1>{};
+        if (split && sp) return hipErrorInvalidValue;
+        if (split == 1)
+            return dispatch_half<Real, RED_QUARTIC, 1>(N, psi, x0, xc, S, se, pk, none, HB_TOP, st,
+                                                       ss);
+    }
+    if (split) return hipErrorInvalidValue;
     if (hist)
-        return dispatch_half<Real, RED_HIST>(N, psi, x0, xc, S, pk, *sp,
-                                             herm || sizeof(Real) == 8 ? HB_TOP : HB_LAST, st, hs);
-    if (sp) return dispatch_half<Real, RED_GEN>(N, psi, x0, xc, S, pk, *sp, HB_TOP, st, ns);
-    return dispatch_half<Real, RED_QUARTIC>(N, psi, x0, xc, S, pk, Spec{}, HB_TOP, st, ns);
+        return dispatch_half<Real, RED_HIST, 0>(N, psi, x0, xc, S, se, pk, *sp,
+                                                herm || sizeof(Real) == 8 ? HB_TOP : HB_LAST, st,
+                                                hs);
+    if (sp) return dispatch_half<Real, RED_GEN, 0>(N, psi, x0, xc, S, se, pk, *sp, HB_TOP, st, ns);
+    return dispatch_half<Real, RED_QUARTIC, 0>(N, psi, x0, xc, S, se, pk, none, HB_TOP, st, ns);
 }
-template hipError_t launch_half<float>(const void*, int, bool, int64_t, int64_t, double*,
-                                       const Pack&, const Spec*, hipStream_t);
-template hipError_t launch_half<double>(const void*, int, bool, int64_t, int64_t, double*,
-                                        const Pack&, const Spec*, hipStream_t);
+template hipError_t launch_half<float>(const void*, int, bool, int, int64_t, int64_t, double*,
+                                       const int*, const Pack&, const Spec*, hipStream_t);
+template hipError_t launch_half<double>(const void*, int, bool, int, int64_t, int64_t, double*,
+                                        const int*, const Pack&, const Spec*, hipStream_t);
 
 }  // namespace sre2

@@ -81,9 +81,9 @@ template <typename Real> int64_t pass2_col_tiles(int N, int slab);
 
 // Row bits up to which pass 2 is a single round.
 template <typename Real> int pass2_round_bits();
-// N evaluated on chip by half transforms (all forms but the split ones; hist:
-// for the histogram).
-template <typename Real> bool half_takes(int N, bool hist);
+// N evaluated on chip by half transforms (hist: for the histogram; split: for
+// a split form, from shift 1 on: FP16 halves only).
+template <typename Real> bool half_takes(int N, bool hist, int split);
 
 // S[i] = S_{x0+i} for shifts [x0, x0 + xc): the half transforms where they take
 // N (herm: a Hermitian-pair form); else the tiny kernel (plain, N < RB) or the
@@ -99,18 +99,22 @@ hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int
                                const Spec* sp, hipStream_t st);
 // The half transforms of launch_shift_kernel.
 template <typename Real>
-hipError_t launch_half(const void* psi, int N, bool herm, int64_t x0, int64_t xc, double* S, const Pack& pk,
-                       const Spec* sp, hipStream_t st);
+hipError_t launch_half(const void* psi, int N, bool herm, int split, int64_t x0, int64_t xc,
+                       double* S, const int* se, const Pack& pk, const Spec* sp, hipStream_t st);
 // Two-pass slab kinds: the full slab of 2^N values per shift; the Hermitian
 // pair's half slab (2^(N-1) values, rows of pass1_row_bits(N - 1) bits); the
 // row pairs of the plain and split forms (half the rows of the full slab,
 // rows of pass1_row_bits(N) bits); a full slab whose two halves pass 2
 // transforms apart (row pairs switched off: S_x of the plain M2 forms bit for
-// bit that of the row pairs).  The last three need x >= 2^L.
+// bit that of the row pairs); the row pairs of the BF16 split form up to
+// kImagesMaxN, whose left-out rows pass 2 rebuilds.  All but the first need
+// x >= 2^L.
 constexpr int kSlabFull = 0;
 constexpr int kSlabHerm = 1;
 constexpr int kSlabPairs = 2;
 constexpr int kSlabBoth = 3;
+constexpr int kSlabImages = 4;
+constexpr int kImagesMaxN = 16;
 // First shift of the row-pair range (shifts below it take the full slab):
 // 2^L, or 2^(L + r) when the plain column transform of a full slab takes a
 // half-LDS tile (r: the lowest register row bit of its plan); 2^N when N is

@@ -85,7 +85,7 @@ void k_pass2(const typename CT<Real>::T* __restrict__ scratch, int NS, int P,
     // a zero inserted at bit j, which keeps bits disjoint.
     const uint32_t base = thread_base<r0.lperm, r0.wave>();
     int j = 0;
-    if constexpr (HALF == HALF_BOTH) j = half_row_bit((uint32_t)((uint64_t)(x0 + s) >> L));
+    if constexpr (HALF == HALF_BOTH) j = half_row_bit((uint32_t)((uint64_t)(x0 + s) >> L), 0u);
     const auto row_of = [&](uint32_t r) { return HALF == HALF_BOTH ? insert0(r, (uint32_t)j) : r; };
     const uint32_t vb = (row_of(base >> CB) << L) + (base & CMASK);
     double acc = 0.0;
@@ -212,14 +212,16 @@ template <typename Real>
 hipError_t launch_pass2(const void* scratch, int N, int slab, int split, int64_t x0, int cs,
                         int P, double* part, const int* se, const Spec* sp, hipStream_t st) {
     if (N <= Tune<Real>::FMAX || N > max_n_of<Real>()) return hipErrorInvalidValue;
-    if (slab < kSlabFull || slab > kSlabBoth || split < 0 || split > 2 ||
+    if (slab < kSlabFull || slab > kSlabImages || split < 0 || split > 2 ||
         (split && (slab == kSlabHerm || sizeof(Real) != 4)) ||
-        (slab == kSlabBoth && (sp || split)))
+        (slab == kSlabBoth && (sp || split)) ||
+        (slab == kSlabImages && (sp || split != 2 || N > kImagesMaxN)))
         return hipErrorInvalidValue;
     int NS, L;
     slab_geometry<Real>(N, slab, &NS, &L);
-    if ((slab == kSlabPairs || slab == kSlabBoth) && x0 < pair_first_shift<Real>(N, split))
+    if (slab != kSlabFull && slab != kSlabHerm && x0 < pair_first_shift<Real>(N, split))
         return hipErrorInvalidValue;
+    if (slab == kSlabImages) return launch_pass2_images(scratch, N, x0, cs, P, part, se, st);
     const bool half = slab == kSlabHerm || slab == kSlabPairs;
     const int HT = NS - L - (slab == kSlabBoth ? 1 : 0);
     constexpr int HMAX = pass2_max_rows<Real>();

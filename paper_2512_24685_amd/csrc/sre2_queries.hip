@@ -27,7 +27,7 @@ int herm_min_n() {
 template <typename Real>
 int64_t pass2_col_tiles(int N, int slab) {
     const int L = row_bits_of<Real>(slab == kSlabHerm ? N - 1 : N);
-    const int HT = N - L - (slab == kSlabFull ? 0 : 1);
+    const int HT = N - L - (slab == kSlabFull || slab == kSlabImages ? 0 : 1);
     const int tb = HT >= 1 && HT <= Prec<Real>::MAXTB ? pass2_tb<Real>(HT) : 0;
     return tb > 0 ? (int64_t)1 << (L + HT - tb) : 0;
 }
@@ -37,12 +37,13 @@ int pass2_round_bits() {
 }
 template int pass2_round_bits<float>();
 template <typename Real>
-bool half_takes(int N, bool hist) {
+bool half_takes(int N, bool hist, int split) {
+    if (split) return split == 1 && N >= Tune<Real>::HSPLIT && N <= Tune<Real>::HMAX;
     return hist ? N >= half_hist_min<Real>() && N <= half_hist_max<Real>()
                 : N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX;
 }
-template bool half_takes<float>(int, bool);
-template bool half_takes<double>(int, bool);
+template bool half_takes<float>(int, bool, int);
+template bool half_takes<double>(int, bool, int);
 template int max_n<float>();
 template int max_n<double>();
 template int fused_max_n<float>();

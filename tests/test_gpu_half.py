@@ -1,7 +1,9 @@
 """The on-chip half transforms (k_half) at the edges of their range, against
 the FP64 CPU oracle: ranges that are shift 0 alone, start or end at it, or
-hold the last shifts; the smallest and largest N per precision and the sizes
-where shift 0 changes route (FP32: on chip up to N = 14, two-pass above).
+hold the last shifts; the smallest and largest N per precision, and the FP16
+split form, whose shift 0 takes another kernel (k_fused up to N = 14, two-pass
+above); and the BF16 form's rebuilt rows (k_pass2_images) with the left-out row
+bit in a register and in the thread index.
 
 Tolerances: an S_x is a sum of 2^N fourth powers whose values carry the
 rounding of N - 1 additions each (relative to the largest |W|, which is n at
@@ -17,7 +19,8 @@ pytestmark = pytest.mark.gpu
 
 import paper_2512_24685_amd as sre2  # noqa: E402
 
-TOL_SX = {"fp32": 1e-4, "fp32h": 1e-4, "fp64": 1e-11, "fp64h": 1e-11}
+TOL_SX = {"fp32": 1e-4, "fp32h": 1e-4, "split16": 1e-4, "splitbf16": 1e-4,
+          "fp64": 1e-11, "fp64h": 1e-11}
 
 
 def dev(psi):
@@ -31,8 +34,11 @@ def _gpu():
 
 
 @pytest.mark.parametrize("form,N", [("fp32", 10), ("fp32", 11), ("fp32", 12), ("fp32", 14),
-                                    ("fp32", 15), ("fp32", 16), ("fp32h", 16), ("fp64", 10), ("fp64", 11), ("fp64", 13), ("fp64", 14),
-                                    ("fp64h", 15)])
+                                    ("fp32", 15), ("fp32", 16), ("fp32h", 16),
+                                    ("split16", 13), ("split16", 14), ("split16", 15),
+                                    ("split16", 16), ("splitbf16", 15),
+                                    ("splitbf16", 16), ("fp64", 10), ("fp64", 11), ("fp64", 13),
+                                    ("fp64", 14), ("fp64h", 15)])
 def test_range_edges(oracle_mod, form, N):
     c128 = form.startswith("fp64")
     psi = W.haar(N, 4200 + N, np.complex128 if c128 else np.complex64)
