@@ -82,7 +82,8 @@ def slab_ranges(N: int, form: str, x0: int, xc: int):
     shift in pass 2, shifts).  Shifts below 2^L take the full slab of 2^N
     values; above (from `sre2_half_slab_first_shift`), the Hermitian-pair
     forms and (row pairs, on by default) the plain and split forms take half
-    slabs of 2^(N-1) values, which pass 2 transforms as they are."""
+    slabs of 2^(N-1) values, which pass 2 transforms as they are (BF16 from
+    N = 17 on)."""
     import paper_2512_24685_amd as sre2
 
     herm = form.endswith("h")
@@ -95,7 +96,9 @@ def slab_ranges(N: int, form: str, x0: int, xc: int):
     lo = max(0, min(x0 + xc, first) - x0)
     out = [(1 << N, Lf, 1 << N, lo)] if lo else []
     if xc > lo:
-        out.append((1 << (N - 1), Lh, 1 << (N - 1), xc - lo))
+        # the BF16 form's pass 2 rebuilds the rows up to N = 16
+        tvals = 1 << (N if form == "splitbf16" and N <= 16 else N - 1)
+        out.append((1 << (N - 1), Lh, tvals, xc - lo))
     return out
 
 
@@ -152,11 +155,11 @@ def roofline(N, form, kind, ms, launches, traffic, evals=1, x0=0, xc=None):
                        hbm_GBs=round(gbs, 1), hbm_frac=round(gbs / HBM_PEAK_GBS, 4))
         return ent
     # on-chip kernels: every value stays on chip; VALU-bound.  The plain and
-    # Hermitian forms take half transforms from N = 10 on; below,
-    # the Hermitian forms run x = 0 as a separate short plain launch, so the
+    # Hermitian forms take half transforms from N = 10 on, split16 from 13;
+    # below, the Hermitian forms run x = 0 as a separate short plain launch, so the
     # work and the time are taken per evaluation (all launches of the class)
     # rather than per launch.
-    half = N >= 10 and not form.startswith("split")
+    half = N >= (13 if form == "split16" else 10) and form != "splitbf16"
     herm = form.endswith("h") or half
     nt = N - (1 if herm else 0)
     ops = (4 + 2 * nt + (6 if herm else 5)) * (1 << N) * (1 << nt)
@@ -164,7 +167,8 @@ def roofline(N, form, kind, ms, launches, traffic, evals=1, x0=0, xc=None):
     alu = ops / per_eval_s
     return {"bound": "alu", "achieved": round(alu / 1e12, 3), "peak": round(VALU_PEAK_OPS / 1e12, 2),
             "unit": "Tops/s", "frac": round(alu / VALU_PEAK_OPS, 4), "traffic": traffic,
-            "kernel": "k_half" if half else "k_fused", "avg_launch_us": round(avg_s * 1e6, 2), "launches": launches,
+            "kernel": "k_half" if half else "k_fused", "avg_launch_us": round(avg_s * 1e6, 2),
+            "launches": launches,
             "class_us_per_evaluation": round(per_eval_s * 1e6, 2),
             "alg_ops_per_evaluation": ops}
 

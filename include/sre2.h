@@ -77,7 +77,8 @@ extern "C" {
  * 2^14, is split into FP16 hi + lo halves, and v_mfma_f32_16x16x32_f16 applies
  * the exact +-1 matrix to both with FP32 accumulation (the scale is removed in
  * FP64 at the end).  Stages left over (N mod 4) use FP32 butterflies; N < 5
- * uses the FP32 kernel. */
+ * uses the FP32 kernel.  For 13 <= N <= 16 the shifts x >= 1 run on chip as
+ * half transforms. */
 #define SRE2_FORM_SPLIT_F16 1
 /* SPLIT_BF16: the same factors on v_mfma_f32_16x16x32_bf16 with BF16 hi + lo
  * halves (16 significant bits per value instead of 22; BF16 has FP32's
@@ -90,8 +91,8 @@ extern "C" {
  * conj f_x(k) (from Eq. Pauli_expect), so with j the top set bit of x the
  * transform of f_x restricted to the half-space k_j = 0 gives every W_x(z):
  * W_x(z) = 2 Re or 2i Im of it, and S_x = 16 sum (Re^4 + Im^4).  Shift 0 (and,
- * for N >= 15 in FP32 / 14 in FP64, the shifts below 2^12 / 2^11) use the plain
- * kernels. */
+ * for N >= 17 in FP32 / 16 in FP64, the shifts below 2^L of sre2_row_bits) use
+ * the plain transform. */
 #define SRE2_FORM_FP32_HERM 4
 #define SRE2_FORM_FP64_HERM 5
 
@@ -146,7 +147,10 @@ int sre2_set_scratch_limit(sre2_ctx* ctx, size_t bytes);
  * from the full slab's by rounding only, within the same error bound.  The
  * general index (sre2_sre) takes the row pairs too, and the spectrum
  * (sre2_pauli_spectrum) in FP64 and, up to N = 17, in FP32 (its counts are
- * those of the full slab).  Sizes evaluated on chip have no slab.  Errors: SRE2_EINVAL (ctx == NULL). */
+ * those of the full slab).  SPLIT_BF16 at N = 15 and 16 rebuilds the left-out
+ * rows in pass 2 instead (j then a bit that pass 2 holds in registers, when
+ * x >> L has one), so that its results keep their bits.  Sizes evaluated on
+ * chip have no slab.  Errors: SRE2_EINVAL (ctx == NULL). */
 int sre2_set_row_pairs(sre2_ctx* ctx, int enable);
 
 /* First shift x of an N-qubit evaluation that takes a half slab in the

@@ -32,8 +32,9 @@ __device__ __forceinline__ void final_out(double S, double n, double bad, int N,
 // (grid y: state of a pack): sum of S_x, FP64 norm and non-finite count of psi,
 // M and status.  Small calls are launches and little else: the norm, its
 // partials' sum, the sum of S_x and the logarithm as kernels of their own cost
-// 3 to 4 us each, this one 4.5 to 7 (N = 10 to 14); beyond, one workgroup's
-// share of the bandwidth is less than what the launches cost.  Fixed order.
+// 2.5 to 4 us each with the gaps between them, this one 2.9 (N = 10) to 6.2
+// (N = 14; N = 10 call 21.7 -> 13.4 us).  Beyond N = 14 one workgroup takes
+// longer to read the state than the three launches it saves.  Fixed order.
 constexpr int kFinishMaxN = 14;
 constexpr int kFinishThreads = 1024;
 template <typename C, int IT>  // IT values per thread: 2^N = 1024 IT, or less with IT = 1

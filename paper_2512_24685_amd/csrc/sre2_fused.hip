@@ -1,5 +1,7 @@
 // sre2_fused.hip - whole transforms on chip: k_tiny and k_fused (N below the
-// half transforms; the split forms up to the largest tile), and the launcher of every on-chip shift sum.
+// half transforms; the split forms below theirs, the BF16 form and the FP16
+// form's shift 0 up to the largest tile), and the launcher of every on-chip
+// shift sum.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -62,9 +64,10 @@ __host__ __device__ constexpr bool fused_keeps_psi(int NT, bool herm) {
 
 // ---------------------------------------------------------------------------
 // Fused: whole transforms of NT bits in a 2^TB tile of SPT = 2^(TB-NT) shifts.
-// From N = 10 on only the split forms take it (and the FP32 spectrum up to 11): the
-// half transforms of k_half do half the work and hold twice the waves (N = 14
-// FP32 450 -> 147 us, N = 13 FP64 142 -> 90 us per evaluation).
+// From N = 10 on only the split forms take it (FP16 up to 12 and for shift 0,
+// BF16 up to 14; and the FP32 spectrum up to 11): the half transforms of k_half
+// do half the work and hold twice the waves (N = 14 FP32 450 -> 150 us, FP16
+// 442 -> 156 us, N = 13 FP64 142 -> 60 us per evaluation).
 //  HERM = false: NT = N, the tile element (slot j, k) is f_x(k), x = x0 + j.
 //  HERM = true : NT = N - 1 (Hermitian pair, x >= 1): with hb the top set bit
 //                of x, element (j, k') is f_x(k) for k = k' with a 0 inserted
@@ -316,7 +319,8 @@ hipError_t launch_shift_kernel(const void* psi, int N, bool herm, int split, int
                                const Spec* sp, hipStream_t st) {
     const bool hist = sp && sp->kind == kRedHist;
     // (the split forms' shift 0 goes through k_fused)
-    const bool half = split  ? split == 1 && x0 > 0 && N >= Tune<Real>::HSPLIT && N <= Tune<Real>::HMAX
+    const bool half = split  ? split == 1 && x0 > 0 && N >= Tune<Real>::HSPLIT &&
+                                  N <= Tune<Real>::HMAX
                       : hist ? N >= half_hist_min<Real>() && N <= half_hist_max<Real>()
                              : N >= Tune<Real>::HMIN && N <= Tune<Real>::HMAX;
     if ((N > Tune<Real>::FMAX && !half) || split < 0 || split > 2 ||
