@@ -37,14 +37,15 @@ __device__ __forceinline__ void final_out(double S, double n, double bad, int N,
 // longer to read the state than the three launches it saves.  Fixed order.
 constexpr int kFinishMaxN = 14;
 constexpr int kFinishThreads = 1024;
-template <typename C, int IT>  // IT values per thread: 2^N = 1024 IT, or less with IT = 1
+// IT values per thread: 2^N = 1024 IT, or less with IT = 1
+template <typename C, int IT, typename PackT>
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const C* __restrict__ psi,
                                                            const double* __restrict__ Sx, int N,
                                                            double* __restrict__ out,
-                                                           const Pack pk, int kind, double alpha) {
+                                                           const PackT pk, int kind, double alpha) {
     constexpr int NW = kFinishThreads / 64;
     __shared__ double red[3][NW];
-    if (pk.count) {
+    if constexpr (is_packed<PackT>) {
         psi = (const C*)pk.psi[blockIdx.y];
         Sx = pk_sx(pk.ws[blockIdx.y], pk.N);
         out = pk.out[blockIdx.y];
@@ -84,26 +85,39 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const C* __restrict__
     }
 }
 
-template <typename C>
-hipError_t launch_finish_of(const void* psi, const double* Sx, int N, double* out, const Pack& pk,
-                            int kind, double alpha, hipStream_t st) {
-    const dim3 grid(1, (unsigned)(pk.count ? pk.count : 1)), block(kFinishThreads);
+template <typename C, typename PackT>
+hipError_t launch_finish_of(const void* psi, const double* Sx, int N, double* out, const PackT& pk,
+                            int count, int kind, double alpha, hipStream_t st) {
+    const dim3 grid(1, (unsigned)count), block(kFinishThreads);
     const C* p = (const C*)psi;
     switch (N <= 10 ? 10 : N) {
-        case 10: k_finish<C, 1><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha); break;
-        case 11: k_finish<C, 2><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha); break;
-        case 12: k_finish<C, 4><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha); break;
-        case 13: k_finish<C, 8><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha); break;
-        case 14: k_finish<C, 16><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha); break;
+        case 10:
+            k_finish<C, 1, PackT><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha);
+            break;
+        case 11:
+            k_finish<C, 2, PackT><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha);
+            break;
+        case 12:
+            k_finish<C, 4, PackT><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha);
+            break;
+        case 13:
+            k_finish<C, 8, PackT><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha);
+            break;
+        case 14:
+            k_finish<C, 16, PackT><<<grid, block, 0, st>>>(p, Sx, N, out, pk, kind, alpha);
+            break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 inline hipError_t launch_finish(const void* psi, int dtype, const double* Sx, int N, double* out,
                                 const Pack& pk, int kind, double alpha, hipStream_t st) {
-    return dtype == kC64
-               ? launch_finish_of<float2>(psi, Sx, N, out, pk, kind, alpha, st)
-               : launch_finish_of<double2>(psi, Sx, N, out, pk, kind, alpha, st);
+    const bool f32 = dtype == kC64;
+    if (pk.count)
+        return f32 ? launch_finish_of<float2>(psi, Sx, N, out, pk, pk.count, kind, alpha, st)
+                   : launch_finish_of<double2>(psi, Sx, N, out, pk, pk.count, kind, alpha, st);
+    return f32 ? launch_finish_of<float2>(psi, Sx, N, out, NoPack{}, 1, kind, alpha, st)
+               : launch_finish_of<double2>(psi, Sx, N, out, NoPack{}, 1, kind, alpha, st);
 }
 
 }  // namespace sre2

@@ -16,11 +16,11 @@ namespace sre2 {
 // ---------------------------------------------------------------------------
 // Tiny N (N < RB): one thread per shift.
 // ---------------------------------------------------------------------------
-template <typename Real, int N, bool GEN>
+template <typename Real, int N, bool GEN, typename PackT>
 __global__ __launch_bounds__(64) void k_tiny(const typename CT<Real>::T* __restrict__ psi,
                                              int64_t x_begin, int64_t x_count,
                                              double* __restrict__ S_out,
-                                             const Pack pk, const Spec sp) {
+                                             const PackT pk, const Spec sp) {
     using C = typename CT<Real>::T;
     constexpr int D = 1 << N;
     __shared__ unsigned lh[GEN ? kMaxBins * kHistCopies : 1];
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(64) void k_tiny(const typename CT<Real>::T* __restr
         hist_flush(lh, sp);
         return;
     }
-    if (pk.count) {
+    if constexpr (is_packed<PackT>) {
         psi = (const C*)pk.psi[blockIdx.y];
         S_out = pk_sx(pk.ws[blockIdx.y], N) + x_begin;
     }
@@ -76,7 +76,7 @@ __host__ __device__ constexpr bool fused_keeps_psi(int NT, bool herm) {
 //                Re or twice i Im of this half transform, so
 //                S_x = 16 sum_z' (Re^4 + Im^4).
 // ---------------------------------------------------------------------------
-template <typename Real, int NT, int TB, int RB, bool HERM, int SPLIT, bool GEN>
+template <typename Real, int NT, int TB, int RB, bool HERM, int SPLIT, bool GEN, typename PackT>
 __global__ __launch_bounds__(1 << (TB - RB))
 __attribute__((amdgpu_waves_per_eu(SPLIT ? SRE2_FUSEDS_WAVES
                                    : (fused_half<Real>(NT)
@@ -85,7 +85,7 @@ __attribute__((amdgpu_waves_per_eu(SPLIT ? SRE2_FUSEDS_WAVES
                                           : SRE2_FUSED_WAVES))))
 void k_fused(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64_t x_count,
              double* __restrict__ S_out, const int* __restrict__ scale_exp,
-             const Pack pk, const Spec sp) {
+             const PackT pk, const Spec sp) {
     using C = typename CT<Real>::T;
     constexpr int T = 1 << (TB - RB);
     constexpr int PK = 1000 + NT + 10000 * SPLIT;
@@ -101,7 +101,7 @@ void k_fused(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int6
     __shared__ C lds[NL > NRED ? NL : NRED];
     __shared__ unsigned lh[GEN ? kMaxBins * kHistCopies : 1];
     double* red = reinterpret_cast<double*>(lds);
-    if (pk.count) {
+    if constexpr (is_packed<PackT>) {
         psi = (const C*)pk.psi[blockIdx.y];
         S_out = pk_sx(pk.ws[blockIdx.y], pk.N) + x_begin;
         scale_exp = pk_se(pk.ws[blockIdx.y], pk.N);
@@ -233,8 +233,15 @@ hipError_t launch_tiny_n(const void* psi, int64_t x0, int64_t xc, double* S,
                          const Pack& pk, const Spec& sp, hipStream_t st) {
     using C = typename CT<Real>::T;
     const int64_t blocks = (xc + 63) / 64;
-    hipLaunchKernelGGL((k_tiny<Real, N, GEN>), dim3((unsigned)blocks, (unsigned)(pk.count ? pk.count : 1)), dim3(64), 0, st,
-                       (const C*)psi, x0, xc, S, pk, sp);
+    if constexpr (!GEN) {
+        if (pk.count) {
+            k_tiny<Real, N, GEN, Pack><<<dim3((unsigned)blocks, (unsigned)pk.count), 64, 0, st>>>(
+                (const C*)psi, x0, xc, S, pk, sp);
+            return hipGetLastError();
+        }
+    }
+    k_tiny<Real, N, GEN, NoPack><<<dim3((unsigned)blocks), 64, 0, st>>>((const C*)psi, x0, xc, S,
+                                                                        NoPack{}, sp);
     return hipGetLastError();
 }
 
@@ -252,12 +259,22 @@ hipError_t launch_fused_nt(const void* psi, int64_t x0, int64_t xc, double* S, c
     int64_t cap = 65536;
     if constexpr (fused_keeps_psi<Real>(NT, HERM)) {
         static const int64_t resident = resident_workgroups(
-            reinterpret_cast<const void*>(&k_fused<Real, NT, TB, RB, HERM, SPLIT, GEN>), 1 << (TB - RB));
+            reinterpret_cast<const void*>(&k_fused<Real, NT, TB, RB, HERM, SPLIT, GEN, NoPack>),
+            1 << (TB - RB));
         cap = 2 * resident;
     }
     const int64_t grid = ntiles < cap ? ntiles : cap;
-    hipLaunchKernelGGL((k_fused<Real, NT, TB, RB, HERM, SPLIT, GEN>), dim3((unsigned)grid, (unsigned)(pk.count ? pk.count : 1)),
-                       dim3(1 << (TB - RB)), 0, st, (const C*)psi, x0, xc, S, se, pk, sp);
+    const dim3 block(1 << (TB - RB));
+    if constexpr (!GEN) {
+        if (pk.count) {
+            k_fused<Real, NT, TB, RB, HERM, SPLIT, GEN, Pack>
+                <<<dim3((unsigned)grid, (unsigned)pk.count), block, 0, st>>>((const C*)psi, x0, xc,
+                                                                            S, se, pk, sp);
+            return hipGetLastError();
+        }
+    }
+    k_fused<Real, NT, TB, RB, HERM, SPLIT, GEN, NoPack><<<dim3((unsigned)grid), block, 0, st>>>(
+        (const C*)psi, x0, xc, S, se, NoPack{}, sp);
     return hipGetLastError();
 }
 

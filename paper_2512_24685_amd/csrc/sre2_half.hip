@@ -176,11 +176,11 @@ enum HalfBit { HB_TOP, HB_LAST };
 // of the form take it.  The BF16 form is not taken here: under another order its
 // 16-bit halves move the S_x of N = 13 to 16 by 2e-9 to 1.5e-8 (2-norm), FP16's
 // 22 bits by 4e-10 or less.
-template <typename Real, int NT, int RB, int RED, int SPLIT>
+template <typename Real, int NT, int RB, int RED, int SPLIT, typename PackT>
 __global__ __launch_bounds__(1 << (NT - RB))
 __attribute__((amdgpu_waves_per_eu(half_waves_per_simd<Real>(RB))))
 void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64_t x_count,
-            double* __restrict__ S_out, const int* __restrict__ scale_exp, const Pack pk,
+            double* __restrict__ S_out, const int* __restrict__ scale_exp, const PackT pk,
             const Spec sp, int bit) {
     static_assert(!SPLIT || (RED == RED_QUARTIC && sizeof(Real) == 4), "split forms: M2 in FP32");
     using C = typename CT<Real>::T;
@@ -193,7 +193,7 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
     __shared__ Real lds[HR::NV];
     __shared__ double red[NW];
     __shared__ unsigned lh[RED == RED_HIST ? kMaxBins * kHistCopies : 1];
-    if (pk.count) {
+    if constexpr (is_packed<PackT>) {
         psi = (const C*)pk.psi[blockIdx.y];
         S_out = pk_sx(pk.ws[blockIdx.y], N) + x_begin;
         scale_exp = pk_se(pk.ws[blockIdx.y], N);
@@ -330,9 +330,18 @@ hipError_t launch_half_n(const void* psi, int64_t x0, int64_t xc, double* S, con
     constexpr int RB = half_rb<Real>(N, RED == RED_HIST || SPLIT);
     const int64_t blocks =
         RED != RED_HIST ? xc : ((xc + 3) / 4 < kHistBlocks ? (xc + 3) / 4 : kHistBlocks);
-    hipLaunchKernelGGL((k_half<Real, N - 1, RB, RED, SPLIT>),
-                       dim3((unsigned)blocks, (unsigned)(pk.count ? pk.count : 1)),
-                       dim3(1 << (N - 1 - RB)), 0, st, (const C*)psi, x0, xc, S, se, pk, sp, bit);
+    const dim3 block(1 << (N - 1 - RB));
+    if constexpr (RED == RED_QUARTIC && N <= Tune<Real>::FMAX) {
+        if (pk.count) {
+            k_half<Real, N - 1, RB, RED, SPLIT, Pack>
+                <<<dim3((unsigned)blocks, (unsigned)pk.count), block, 0, st>>>(
+                    (const C*)psi, x0, xc, S, se, pk, sp, bit);
+            return hipGetLastError();
+        }
+    }
+    if (pk.count) return hipErrorInvalidValue;
+    k_half<Real, N - 1, RB, RED, SPLIT, NoPack><<<dim3((unsigned)blocks), block, 0, st>>>(
+        (const C*)psi, x0, xc, S, se, NoPack{}, sp, bit);
     return hipGetLastError();
 }
 

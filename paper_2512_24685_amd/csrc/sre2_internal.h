@@ -27,6 +27,12 @@ struct Pack {
     double* ws[kMaxPack] = {};
     double* out[kMaxPack] = {};
 };
+// The argument of single-state launches in its place: the host takes 4.5 us
+// for a launch with 1.5 KB of kernel arguments and 2.9 us for one with a few
+// pointers, and calls of N <= 11 wait for the host (N = 10: 11.2 -> 9.7 us).
+struct NoPack {};
+template <typename PackT>
+constexpr bool is_packed = sizeof(PackT) == sizeof(Pack);
 
 __host__ __device__ inline int64_t pack_ws_doubles(int N) {
     return ((int64_t)1 << N) + 3 * kMaxRed + 1;

@@ -66,14 +66,14 @@ constexpr int kRedThreads = 256;
 static_assert(kRedThreads <= kMaxRed, "reduction blocks");
 
 // part[b] = sum of |psi|^2 over block b's fixed range; flag[b] = non-finite seen.
-template <typename C>
+template <typename C, typename PackT>
 __global__ __launch_bounds__(kRedThreads) void k_norm_part(const C* __restrict__ psi, int64_t n,
                                                            int64_t per_block,
                                                            double* __restrict__ part,
                                                            double* __restrict__ flag,
-                                                           const Pack pk) {
+                                                           const PackT pk) {
     __shared__ double red[kRedThreads];
-    if (pk.count) {
+    if constexpr (is_packed<PackT>) {
         psi = (const C*)pk.psi[blockIdx.y];
         part = pk_npart(pk.ws[blockIdx.y], pk.N);
         flag = pk_nflag(pk.ws[blockIdx.y], pk.N);
@@ -187,10 +187,11 @@ __global__ __launch_bounds__(kRedThreads) void k_final(const double* __restrict_
 // s = 14 - ceil(log2 n) from the norm partials (0 when n is not positive and
 // finite): with every |value| of a transform bounded by n, the scaled values
 // of the split form stay below 2^14, inside FP16's range.
+template <typename PackT>
 __global__ void k_split_scale(const double* __restrict__ npart, int nb, int* __restrict__ se,
-                              const Pack pk) {
+                              const PackT pk) {
     if (threadIdx.x != 0) return;
-    if (pk.count) {
+    if constexpr (is_packed<PackT>) {
         npart = pk_npart(pk.ws[blockIdx.y], pk.N);
         se = pk_se(pk.ws[blockIdx.y], pk.N);
     }
@@ -205,8 +206,10 @@ __global__ void k_split_scale(const double* __restrict__ npart, int nb, int* __r
 }
 
 hipError_t launch_split_scale(const double* npart, int nb, int* se, const Pack& pk, hipStream_t st) {
-    hipLaunchKernelGGL(k_split_scale, dim3(1, (unsigned)(pk.count ? pk.count : 1)), dim3(64), 0, st, npart, nb, se,
-                       pk);
+    if (pk.count)
+        k_split_scale<<<dim3(1, (unsigned)pk.count), 64, 0, st>>>(npart, nb, se, pk);
+    else
+        k_split_scale<<<1, 64, 0, st>>>(npart, nb, se, NoPack{});
     return hipGetLastError();
 }
 
@@ -224,17 +227,22 @@ hipError_t launch_convert(const void* in, int in_dtype, void* out, int out_dtype
     return hipGetLastError();
 }
 
+template <typename C>
+hipError_t launch_norm_of(const void* psi, int64_t n, int nblocks, double* part, double* flag,
+                          const Pack& pk, hipStream_t st) {
+    const int64_t per = (n + nblocks - 1) / nblocks;
+    const C* p = (const C*)psi;
+    if (pk.count)
+        k_norm_part<C><<<dim3(nblocks, pk.count), kRedThreads, 0, st>>>(p, n, per, part, flag, pk);
+    else
+        k_norm_part<C><<<nblocks, kRedThreads, 0, st>>>(p, n, per, part, flag, NoPack{});
+    return hipGetLastError();
+}
+
 hipError_t launch_norm(const void* psi, int dtype, int64_t n, int nblocks, double* part,
                        double* flag, const Pack& pk, hipStream_t st) {
-    const int64_t per = (n + nblocks - 1) / nblocks;
-    const dim3 grid(nblocks, pk.count ? pk.count : 1);
-    if (dtype == kC64)
-        hipLaunchKernelGGL((k_norm_part<float2>), grid, dim3(kRedThreads), 0, st,
-                           (const float2*)psi, n, per, part, flag, pk);
-    else
-        hipLaunchKernelGGL((k_norm_part<double2>), grid, dim3(kRedThreads), 0, st,
-                           (const double2*)psi, n, per, part, flag, pk);
-    return hipGetLastError();
+    return dtype == kC64 ? launch_norm_of<float2>(psi, n, nblocks, part, flag, pk, st)
+                         : launch_norm_of<double2>(psi, n, nblocks, part, flag, pk, st);
 }
 
 hipError_t launch_moments(const void* psi, int dtype, int64_t n, int nblocks, double* m,
