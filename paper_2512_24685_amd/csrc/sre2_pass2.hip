@@ -7,6 +7,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "sre2_both.h"
 #include "sre2_twopass.h"
 
 namespace sre2 {
@@ -26,12 +27,15 @@ namespace sre2 {
 //             and S_x = 16 sum (Re^4 + Im^4).
 //  HALF_BOTH  a full slab with that same order of stages (row pairs switched
 //             off): the rows with bit j clear and set are transformed apart
-//             and combined last.  Row identity and column transform hold bit
-//             for bit in the plain forms: the products are exactly conjugate
+//             and combined last, sum of |W|^4 over both of the combined values
+//             (both_terms).  Row identity and column transform hold bit for bit
+//             in the plain forms: the products are exactly conjugate
 //             (cmul_conj_a), and a butterfly network fed an XOR-permuted input
 //             computes the same sums and differences, some of them negated
 //             (u + v = v + u, v - u = -(u - v)); so the combined values are
-//             exactly (2 Re A, 0) and (0, 2 Im A), and S_x keeps every bit.
+//             exactly (2 Re A, 0) and (0, 2 Im A), and S_x has every bit of the
+//             half slab's - from all rows of the slab, and only if they hold
+//             the pairing.
 // (The split forms' H_16 products on the matrix cores sum in an order the
 // permutation does not preserve: their half slabs hold the exact images of
 // the computed stored rows, equal to the full slab's up to rounding.)
@@ -117,25 +121,21 @@ void k_pass2(const typename CT<Real>::T* __restrict__ scratch, int NS, int P,
     constexpr bool PREFETCH =
         !half_lds<Real>(TB) && (!SPLIT || (HALF == HALF_SLAB && TB <= 12)) && !GEN;
     if constexpr (HALF == HALF_BOTH) {
+        constexpr Round rl = PL.r[PL.nrounds - 1];
+        const uint64_t x = (uint64_t)(x0 + s);
+        const uint32_t xl = (uint32_t)x & ((1u << L) - 1u);
+        const uint32_t xt = both_mask((uint32_t)(x >> L), xl, j, CB);
+        const uint32_t odd_t = parity(thread_base<rl.lperm, rl.wave>() & xt);
         for (int ct = c0; ct < c1; ++ct) {
             C v[1 << RB], u[1 << RB];
             load_tile(v, ct, 0);
             load_tile(u, ct, 1);
             run_transform<Real, TB, RB, PK>(lds, v);
             run_transform<Real, TB, RB, PK>(lds, u);
+            const uint32_t odd = odd_t ^ parity(((uint32_t)ct << CB) & xl);
 #pragma unroll
-            for (int i = 0; i < (1 << RB); ++i) {
-                // of the two values along j one is real, the other imaginary
-                // (the zero parts exactly so): their sum holds both
-                C w0, w1, w;
-                w0.x = v[i].x + u[i].x;
-                w0.y = v[i].y + u[i].y;
-                w1.x = v[i].x - u[i].x;
-                w1.y = v[i].y - u[i].y;
-                w.x = w0.x + w1.x;
-                w.y = w0.y + w1.y;
-                acc += abs4h(w);
-            }
+            for (int i = 0; i < (1 << RB); ++i)
+                acc += both_terms(v[i], u[i], odd ^ parity(pdep((uint32_t)i, rl.reg) & xt));
         }
     } else if constexpr (PREFETCH) {
         C va[1 << RB], vn[1 << RB];

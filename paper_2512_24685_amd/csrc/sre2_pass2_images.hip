@@ -24,18 +24,12 @@
 #include <type_traits>
 #include <utility>
 
+#include "sre2_both.h"
 #include "sre2_twopass.h"
 
 namespace sre2 {
 
 namespace {
-
-// Remove bit `b` of `v` (the bits above it move down by one): the inverse
-// of insert0 on values with that bit clear.  Like insert0 it maps disjoint
-// bit sets to disjoint bit sets, so it adds over them.
-__host__ __device__ constexpr uint32_t remove_bit(uint32_t v, int b) {
-    return ((v >> (b + 1)) << b) | (v & ((1u << b) - 1u));
-}
 
 // Flip the sign bits of a complex value's parts by the masks mx, my (each
 // 0 or the sign bit of a float, applied to the high word of a double).
