@@ -373,13 +373,15 @@ struct Guard {
 
 int launched() { return hipGetLastError() == hipSuccess ? SRE2_OK : SRE2_EHIP; }
 
-// From kChebRuns qubits on a workgroup takes four runs: the flips of ten bits
-// stay on chip, at 256 workgroups or more.
-constexpr int kChebRuns = 18;
+// From N = 18 on a workgroup takes four runs: the flips of ten bits stay on
+// chip, at 256 workgroups or more.  From N = 22 on four runs with all their loads in
+// flight need more than 256 registers, which leaves one wave per SIMD: two runs
+// (N = 22: 116 against 100 us per term, N = 24: 535 against 484).
+constexpr int cheb_run_bits(int N) { return N < 18 ? 0 : (N < 22 ? 2 : 1); }
 template <int N>
 void launch_cheb(sre2_sim* s, const double2* cur, double2* older, const Tfim& h, double m0,
                  double m, int k) {
-    constexpr int AB = N >= kChebRuns ? 2 : 0;
+    constexpr int AB = cheb_run_bits(N);
     hipLaunchKernelGGL((k_cheb<N - 8 - AB, AB>), dim3(1u << (N - 8 - AB)), dim3(256), 0, s->st,
                        cur, older, s->acc, h, m0, m, k);
 }
