@@ -108,6 +108,49 @@ __device__ __forceinline__ uint32_t tile_slot(uint32_t e) {
     return e ^ ((e >> 4) & 15u) ^ ((e >> 8) & 15u);
 }
 
+// Row of U times the group's four amplitudes.
+__device__ __forceinline__ double2 gate_row(const double2* u, const double2 (&a)[4]) {
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const double2 c = u[j];
+        re = __builtin_fma(c.x, a[j].x, re);
+        im = __builtin_fma(c.x, a[j].y, im);
+        re = __builtin_fma(-c.y, a[j].y, re);
+        im = __builtin_fma(c.y, a[j].x, im);
+    }
+    return make_double2(re, im);
+}
+// Amplitude of group m with zeros at bits lo < hi.
+__device__ __forceinline__ uint32_t group_base(uint32_t m, uint32_t lo, uint32_t hi) {
+    m = ((m >> lo) << (lo + 1)) | (m & ((1u << lo) - 1u));
+    return ((m >> hi) << (hi + 1)) | (m & ((1u << hi) - 1u));
+}
+
+// One gate on the qubits lo < hi, one thread per group of four amplitudes.  A
+// pass of one gate takes it in place of k_gates: it has no tile to pass through
+// LDS and 260 bytes of arguments instead of 4 KB, which cost the host 0.3 us
+// (N <= 20: 7.9 against 8.2 us a call; N = 21: 8.5 against 9.9, N = 22: 21.2
+// against 23.1, N = 24: 76.3 against 78.5).  Not on the pair (0, 1), where a
+// thread's four amplitudes are neighbours and a wave's loads four lines apart
+// each (N = 21: 14.7 against 10.0, N = 24: 88.7 against 80.2).
+struct Gate {
+    double2 u[16];
+};
+__global__ __launch_bounds__(256) void k_gate(double2* __restrict__ psi, int N, uint32_t lo,
+                                              uint32_t hi, const Gate g) {
+    const uint32_t m = blockIdx.x * 256u + threadIdx.x;
+    if (m >= 1u << (N - 2)) return;
+    const uint32_t k = group_base(m, lo, hi);
+    double2 a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        a[j] = psi[k | (uint32_t)(j & 1) << lo | (uint32_t)(j >> 1) << hi];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        psi[k | (uint32_t)(i & 1) << lo | (uint32_t)(i >> 1) << hi] = gate_row(g.u + 4 * i, a);
+}
+
 // Applies the gates of one pass in order, each thread one group of four
 // amplitudes per gate, through LDS.  What bounds it is the pass over memory
 // (N = 20: 16 MiB read and written) and, per gate, 62 FP64 operations and 128
@@ -142,25 +185,14 @@ __global__ __launch_bounds__(1 << (kTileQubits - 2)) void k_gates(double2* __res
         const uint32_t lo = ps.pair[g] & 255u, hi = ps.pair[g] >> 8;
         // insert zero bits at lo, then hi (the threads above a smaller tile
         // work on slots of their own); slots of disjoint bits combine by XOR
-        uint32_t m = ((tid >> lo) << (lo + 1)) | (tid & ((1u << lo) - 1u));
-        m = ((m >> hi) << (hi + 1)) | (m & ((1u << hi) - 1u));
+        const uint32_t m = group_base(tid, lo, hi);
         const uint32_t s0 = tile_slot(m), sl = tile_slot(1u << lo), sh = tile_slot(1u << hi);
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 4; ++j) a[j] = t[s0 ^ (j & 1 ? sl : 0u) ^ (j & 2 ? sh : 0u)];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            double re = 0.0, im = 0.0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double2 c = ps.u[g][4 * i + j];
-                re = __builtin_fma(c.x, a[j].x, re);
-                im = __builtin_fma(c.x, a[j].y, im);
-                re = __builtin_fma(-c.y, a[j].y, re);
-                im = __builtin_fma(c.y, a[j].x, im);
-            }
-            t[s0 ^ (i & 1 ? sl : 0u) ^ (i & 2 ? sh : 0u)] = make_double2(re, im);
-        }
+        for (int i = 0; i < 4; ++i)
+            t[s0 ^ (i & 1 ? sl : 0u) ^ (i & 2 ? sh : 0u)] = gate_row(&ps.u[g][4 * i], a);
     }
     __syncthreads();
 #pragma unroll
@@ -468,6 +500,26 @@ int apply_gates(sre2_sim* s, const double* gates, const int* pairs, int count) {
             }
         }
         ntodo = left;
+        // U with its index bits in the order of the qubits
+        const auto matrix = [&](int g, bool swap, double2* u) {
+            const double* U = gates + 32 * (size_t)g;
+            for (int e = 0; e < 16; ++e) {
+                const int r = e >> 2, c = e & 3;
+                const int f = swap ? 4 * (r >> 1 | (r & 1) << 1) + (c >> 1 | (c & 1) << 1) : e;
+                u[e] = make_double2(U[2 * f], U[2 * f + 1]);
+            }
+        };
+        if (ps.ngates == 1) {
+            const int a = pairs[2 * taken[0]], b = pairs[2 * taken[0] + 1];
+            const int lo = a < b ? a : b, hi = a < b ? b : a;
+            if (hi > 1) {
+                Gate g;
+                matrix(taken[0], a > b, g.u);
+                hipLaunchKernelGGL(k_gate, dim3(blocks_for(int64_t(1) << (s->N - 2))), dim3(256), 0,
+                                   s->st, s->psi, s->N, (uint32_t)lo, (uint32_t)hi, g);
+                continue;
+            }
+        }
         for (int q = 0; __builtin_popcount(ps.mask) < tb; ++q) ps.mask |= 1u << q;
         for (int q = 0, b = 0, o = tb; q < s->N; ++q)
             ps.qubit[(ps.mask >> q) & 1u ? b++ : o++] = (uint32_t)q;
@@ -477,13 +529,7 @@ int apply_gates(sre2_sim* s, const double* gates, const int* pairs, int count) {
             const uint32_t p1 = __builtin_popcount(ps.mask & ((1u << pr[1]) - 1u));
             const bool swap = p0 > p1;
             ps.pair[i] = swap ? p1 + 256 * p0 : p0 + 256 * p1;
-            const double* U = gates + 32 * (size_t)taken[i];
-            for (int e = 0; e < 16; ++e) {
-                // with the pair swapped the bits of both indices swap too
-                const int r = e >> 2, c = e & 3;
-                const int f = swap ? 4 * (r >> 1 | (r & 1) << 1) + (c >> 1 | (c & 1) << 1) : e;
-                ps.u[i][e] = make_double2(U[2 * f], U[2 * f + 1]);
-            }
+            matrix(taken[i], swap, ps.u[i]);
         }
         hipLaunchKernelGGL(k_gates, dim3(1u << (s->N - tb)), dim3(1 << (kTileQubits - 2)), 0,
                            s->st, s->psi, s->N, ps);
