@@ -7,6 +7,7 @@
 
 #include <type_traits>
 
+#include "sre2_half_map.h"
 #include "sre2_plan.h"
 #include "sre2_internal.h"
 
@@ -208,11 +209,6 @@ __device__ __forceinline__ C load_at(__amdgpu_buffer_rsrc_t rs, uint32_t vidx, u
     C v;
     buf_load<AUX>(rs, vidx * (uint32_t)sizeof(C), sidx * (uint32_t)sizeof(C), v);
     return v;
-}
-
-// Insert a zero bit at position `hb` of `v`.
-__device__ __forceinline__ uint32_t insert0(uint32_t v, uint32_t hb) {
-    return ((v >> hb) << (hb + 1)) | (v & ((1u << hb) - 1u));
 }
 
 // Row bit left out of a half slab (Hermitian pair, row pairs), for the row

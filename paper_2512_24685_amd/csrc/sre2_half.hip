@@ -34,6 +34,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "sre2_half_map.h"
 #include "sre2_tile.h"
 
 namespace sre2 {
@@ -52,13 +53,16 @@ __device__ __forceinline__ C cmul_conj_f(C a, C b) {
 
 // One part (0: re, 1: im) of the registers to (PUT) or from a padded buffer
 // of reals.  Slots are 4 or 8 bytes: with pad<5> 32 consecutive lanes hit 32
-// distinct slots modulo 32, free of conflicts for both.  ds_read / ds_write
-// offsets are 16 bits: slots above kLdsSplit bytes take a second base.
+// distinct slots modulo 32, free of conflicts for both (two lanes share a slot in the
+// last round of N = 10 and 11, which have too few bits to choose from).  ds_read /
+// ds_write offsets are 16 bits: slots above kLdsSplit bytes take a second base,
+// which covers 96 KiB; beyond (the upper slots of the 132 KiB buffers of N = 16
+// in FP32, 15 in FP64) the compiler adds to the address.
 constexpr uint32_t kLdsSplit = 32768;
 template <bool PUT, int PART, int RB, uint32_t REG, uint32_t LPERM, uint32_t WAVE, typename Real,
           typename C>
 __device__ __forceinline__ void lds_part(Real* lds, C (&v)[1 << RB]) {
-    constexpr int SB = 5;
+    constexpr int SB = kHalfSB;
     char* b = reinterpret_cast<char*>(lds) +
               pad16<SB>(thread_base<LPERM, WAVE>()) * (uint32_t)sizeof(Real);
     char* b2 = b + kLdsSplit;
@@ -73,19 +77,12 @@ __device__ __forceinline__ void lds_part(Real* lds, C (&v)[1 << RB]) {
     }
 }
 
-// Plan of the half transform of NT bits (split form s: H_16 factors on the
-// matrix cores, as in the other kernels of the split forms).
-template <int NT, int RB, int SPLIT>
-__host__ __device__ constexpr Plan half_plan() {
-    return SPLIT ? make_split_plan(NT, RB, 5, 0, NT, 0) : make_plan(NT, RB, 5, 0, NT);
-}
-
 // Rounds J .. nrounds - 1 of the half transform.
 template <typename Real, int NT, int RB, int SPLIT, int J>
 struct HalfRunner {
     using C = typename CT<Real>::T;
     static constexpr Plan P = half_plan<NT, RB, SPLIT>();
-    static constexpr int NV = P.nrounds < 2 ? 1 : (int)pad_rt((1u << NT) - 1u, 5) + 1;
+    static constexpr int NV = half_lds_reals(P);
     __device__ __forceinline__ static void math(C (&v)[1 << RB], const op8 amat) {
         constexpr Round c = P.r[J];
         butterflies<RB, c.reg, c.bfly>(v);
@@ -118,39 +115,6 @@ __host__ __device__ constexpr int half_waves_per_simd(int rb) {
     return (1 << rb) * (int)sizeof(Real) > 128 ? 2 : 4;
 }
 
-// The order in which the plain transform of 2^N values butterflies its bits:
-// on chip the top five, the low five, the rest upwards; above (FP32) pass 1's
-// four top row bits of 12, its low four and the rest, then the column bits.
-struct BitOrder {
-    int bit[kMaxTileBits + 1] = {};
-};
-template <typename Real>
-__host__ __device__ constexpr BitOrder plain_order(int N) {
-    BitOrder o{};
-    const bool two = N > Tune<Real>::FMAX;
-    const int rows = two ? Tune<Real>::ROW : N, g = two ? Tune<Real>::RB1 : 5;
-    int n = 0;
-    for (int b = rows - g; b < rows; ++b) o.bit[n++] = b;
-    for (int b = 0; b < rows - g; ++b) o.bit[n++] = b;
-    for (int b = rows; b < N; ++b) o.bit[n++] = b;
-    return o;
-}
-// Shift 0: element bit e of the half transform (its j-th butterfly) is bit
-// plain_order[j] of k; the last of that order packs the halves into the real
-// and imaginary part.
-template <typename Real, int NT, int RB>
-__host__ __device__ constexpr BitOrder zero_map() {
-    constexpr Plan P = half_plan<NT, RB, 0>();
-    constexpr BitOrder o = plain_order<Real>(NT + 1);
-    BitOrder m{};
-    int n = 0;
-    for (int r = 0; r < P.nrounds; ++r)
-        for (int b = 0; b < NT; ++b)
-            if ((P.r[r].bfly >> b) & 1u) m.bit[b] = o.bit[n++];
-    m.bit[NT] = o.bit[n];
-    return m;
-}
-
 // Blocks of a histogram launch: each adds its bins to the global counters once
 // (one block per shift would queue 2^N of them at the same few addresses), and
 // takes four shifts or more.
@@ -158,15 +122,6 @@ constexpr int64_t kHistBlocks = 2048;
 
 // Reductions: the sum of |W|^4, the general sums, the histogram.
 enum HalfRed { RED_QUARTIC, RED_GEN, RED_HIST };
-
-// Which set bit of x is left out (hb).  Any gives S_x.  HB_TOP: the top one.
-// HB_LAST: the one the plain transform of 2^N values butterflies last (its
-// order: the top five bits, the low five, the rest upwards).  With the others
-// transformed in that same order, every later bit is clear in x, so the pair
-// k, k ^ x meets element by element at its stage, whose results are exactly
-// (2 Re, 0) and (0, 2 Im): the values keep every bit of the plain transform,
-// which is what the counts of the plain forms' histogram depend on.
-enum HalfBit { HB_TOP, HB_LAST };
 
 // Block b of the grid takes shift x_begin + b, and with RED_HIST every
 // gridDim.x-th one from there (so that few blocks add to the global counters).
@@ -225,7 +180,7 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
 #pragma unroll
                     for (int b = 0; b < NT; ++b) q |= ((e >> b) & 1u) << map.bit[b];
                     const C c = load_at<C>(rs, q, 0);
-                    lds[pad16<5>(e)] = cmul_conj_a(c, c).x;
+                    lds[pad16<kHalfSB>(e)] = cmul_conj_a(c, c).x;
                 }
             };
             squares(0u);
@@ -237,23 +192,9 @@ void k_half(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64
             // k ^ x; both act on disjoint bits of the thread's and the
             // register's part of e, so the register's part of an address is
             // uniform (a scalar offset)
-            uint32_t hb = 31u - __clz(x);
-            bool top5 = false;
-            if constexpr (RED == RED_HIST) {
-                const uint32_t mid = x & bits_range(5, N - 5), low = x & 31u;
-                if (bit == HB_LAST && (mid | low)) hb = 31u - __clz(mid ? mid : low);
-                top5 = bit == HB_LAST && !(mid | low);
-            }
-            const auto k_of = [&](uint32_t e) {
-                if constexpr (RED == RED_HIST) {
-                    // x has top bits only: the first round keeps the other
-                    // four and takes bit 0 as its last
-                    if (top5)
-                        return ((e << 1) & bits_range(1, N - 5)) |
-                               insert0(((e >> (N - 6)) & 15u) << (N - 5), hb) | (e >> (N - 2));
-                }
-                return insert0(e, hb);
-            };
+            constexpr bool HIST = RED == RED_HIST;
+            const HalfShift hs = half_shift<HIST>(x, N, bit);
+            const auto k_of = [&](uint32_t e) { return half_k<HIST>(e, N, hs); };
             const uint32_t R = k_of(r0.reg);
             const uint32_t kb = k_of(base);
             const uint32_t vb = kb ^ (x & ~R), xr = x & R;
