@@ -53,8 +53,8 @@ VALU_PEAK_OPS = 256 * 64 * 2.4e9
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.json")
 # Code of the two-pass kernels, whose counters are stored.
 KERNEL_SOURCES = ["paper_2512_24685_amd/csrc/" + f for f in
-                  ("sre2_pass1.hip", "sre2_pass2.hip", "sre2_twopass.h", "sre2_tile.h",
-                   "sre2_device.h", "sre2_geometry.h", "sre2_plan.h")]
+                  ("sre2_pass1.hip", "sre2_pass2.hip", "sre2_both.h", "sre2_twopass.h", "sre2_tile.h",
+                   "sre2_device.h", "sre2_half_map.h", "sre2_geometry.h", "sre2_plan.h")]
 
 
 
