@@ -122,8 +122,9 @@ int sre2_create(sre2_ctx** out, int hip_device);
  * accepted. */
 int sre2_destroy(sre2_ctx* ctx);
 
-/* Upper bound for the two-pass scratch slab (N >= 15 in FP32, N >= 14 in
- * FP64); shifts are processed in chunks that fit it (at most 2^L shifts per
+/* Upper bound for the two-pass scratch slab (N >= 17 in the FP32 and N >= 16 in
+ * the FP64 forms; SPLIT_BF16, the FP32 spectrum and shift 0 of SPLIT_F16 from
+ * N = 15); shifts are processed in chunks that fit it (at most 2^L shifts per
  * chunk, L = sre2_row_bits).  Default 32 GiB: larger chunks keep both passes
  * closer to the memory rate.  Values below one shift's slab are raised to one
  * slab.  When the device cannot allocate a call's slab, that call halves its
@@ -158,13 +159,18 @@ int sre2_set_row_pairs(sre2_ctx* ctx, int enable);
  * start at 2^L, or in the plain forms where x >> L reaches the upper row bits
  * when the column transform of a full slab takes a tile above 64 KiB:
  * 2^(L + 5) at N = 22 and 24 in FP32); shifts below it take the full slab.
- * 2^N when N uses the fused kernel.
+ * 2^N when no evaluation of N takes a slab (N <= 14 in the FP32 and split forms,
+ * 15 in FP64).  At N = 15 and 16 of the FP32 forms M2 and the general index run
+ * on chip and only the spectrum takes the slabs this describes, of SPLIT_F16 only
+ * shift 0, in a full one.
  * Host-only.  Returns -1 for invalid arguments. */
 int64_t sre2_half_slab_first_shift(int N, int form);
 
-/* Upper bound of the device workspace (bytes) that calls with these arguments
- * grow the context to, with the current default scratch limit (an M2 call on
- * an N that is evaluated on chip takes less).  0 for invalid arguments. */
+/* Device workspace (bytes) an M2 call with these arguments grows the context
+ * to, with the default scratch limit.  Sizes that M2 evaluates on chip have no
+ * slab (SPLIT_F16 at N = 15 and 16: that of shift 0); the spectrum of the FP32 forms
+ * at N = 15 and 16 does take one, up to the scratch limit.  0 for invalid
+ * arguments. */
 size_t sre2_workspace_bytes(int N, int dtype, int form);
 
 /* M2 of one state (Algorithm 1 over all 2^N shifts).
@@ -270,7 +276,7 @@ int sre2_m2_batched(sre2_ctx* ctx, const void* const* psi_list, const int* N_lis
  * (with that device current).
  *   hip_device  device to run on (made current for the call)
  *   psi, N, dtype, form, stream, out, partials: as sre2_m2
- * Two-pass shapes (N >= 15 in FP32 forms, 14 in FP64 forms) run in chunks
+ * Two-pass shapes (as for sre2_set_scratch_limit) run in chunks
  * of as many shifts as the array holds, so large N is slower than sre2_m2.
  * Limit: the call is accepted when the input copy (dtype != the form's
  * precision), S_x (when partials == NULL), the reduction buffers and one
@@ -289,7 +295,7 @@ int sre2_m2_noalloc(int hip_device, const void* psi, int N, int dtype, int form,
 
 /* ---- measurement ------------------------------------------------------- */
 /* Kernel classes for per-launch timing. */
-#define SRE2_KIND_SHIFT 0 /* k_tiny / k_fused: whole transforms, N <= 14 (FP32), 13 (FP64) */
+#define SRE2_KIND_SHIFT 0 /* whole transforms on chip: k_tiny, k_fused, k_half          */
 #define SRE2_KIND_PASS1 1 /* two-pass row transform (writes the scratch slab)          */
 #define SRE2_KIND_PASS2 2 /* two-pass column transform + |W|^4 (reads the slab)        */
 #define SRE2_KIND_AUX 3   /* conversion, norm, reductions, logarithm                    */
@@ -309,14 +315,14 @@ int sre2_timing_read(sre2_ctx* ctx, double* ms, int64_t* launches);
 /* Two-pass geometry of a full evaluation with this context's scratch limit
  * and row-pair setting: shifts per chunk of the shifts x >= 2^L (most of an
  * evaluation; half slabs in the Hermitian-pair forms and, with row pairs, in
- * the plain and split forms; 0 when N uses the fused kernel) and column
- * groups per shift in pass 2.  Host-only.  Errors: SRE2_EINVAL. */
+ * the plain and split forms; 0 when M2 of the shifts x >= 1 runs on chip) and
+ * column groups per shift in pass 2.  Host-only.  Errors: SRE2_EINVAL. */
 int sre2_chunking(sre2_ctx* ctx, int N, int form, int64_t* shifts_per_chunk, int* groups);
 
 /* Row bits L of pass 1 for (N, form): the slab of NS = N bits (N - 1 in the
  * Hermitian-pair forms) is transformed as 2^(NS - L) rows of 2^L values, then
- * by columns; 0 when N is evaluated by the fused kernel, -1 for invalid
- * arguments. */
+ * by columns; 0 when no evaluation of N takes a slab (as for
+ * sre2_half_slab_first_shift), -1 for invalid arguments. */
 int sre2_row_bits(int N, int form);
 
 /* ---- serving loop (continuous batching) ------------------------------- */

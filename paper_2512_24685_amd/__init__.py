@@ -125,7 +125,7 @@ def half_slab_first_shift(N: int, form: str = "fp32") -> int:
 
 
 def row_bits(N: int, form: str = "fp32") -> int:
-    """Pass-1 row bits for (N, form); 0 for the fused range."""
+    """Pass-1 row bits for (N, form); 0 where no evaluation takes a slab."""
     v = lib().sre2_row_bits(int(N), FORMS[form])
     if v < 0:
         raise SRE2Error(EINVAL, "sre2_row_bits")

@@ -110,6 +110,15 @@ int64_t two_pass_shifts(int N, int form, const Spec* spec, int64_t x0, int64_t x
     if (half_path(N, form, spec)) return is_split(form) && x0 == 0 ? 1 : 0;
     return xc;
 }
+// Whether any evaluation of this size and form takes a slab (the spectrum's
+// range on chip ends before M2's in FP32).
+bool takes_slab(int N, int form) {
+    Spec hist{};
+    hist.kind = kRedHist;
+    const int64_t n = int64_t(1) << N;
+    return two_pass_shifts(N, form, nullptr, 0, n) > 0 ||
+           (!is_split(form) && two_pass_shifts(N, form, &hist, 0, n) > 0);
+}
 int64_t col_tiles(int N, int form, int slab) {
     return is_f64(form) ? pass2_col_tiles<double>(N, slab) : pass2_col_tiles<float>(N, slab);
 }
@@ -704,7 +713,7 @@ int sre2_set_scratch_limit(sre2_ctx* ctx, size_t bytes) {
 int sre2_row_bits(int N, int form) {
     if (N < 1 || N > SRE2_MAX_N || !form_ok(form)) return -1;
     if (N > (is_f64(form) ? max_n<double>() : max_n<float>())) return -1;
-    if (N <= fused_max(form)) return 0;
+    if (!takes_slab(N, form)) return 0;
     return row_bits(form, N - (is_herm(form) ? 1 : 0));
 }
 
@@ -714,9 +723,9 @@ size_t sre2_workspace_bytes(int N, int dtype, int form) {
     const size_t n = size_t(1) << N;
     size_t b = red_doubles() * sizeof(double) + n * sizeof(double);
     if (work_dtype(form) != dtype) b += n * (size_t)elem_bytes(work_dtype(form));
-    if (N > fused_max(form)) {
+    if (const int64_t xc = two_pass_shifts(N, form, nullptr, 0, (int64_t)n)) {
         size_t slab = 0, part = 0;
-        slab_need(N, form, high_slab(N, form, true, nullptr), 0, (int64_t)n, kDefaultScratchLimit, &slab,
+        slab_need(N, form, high_slab(N, form, true, nullptr), 0, xc, kDefaultScratchLimit, &slab,
                   &part);
         b += slab + part * sizeof(double);
     }
@@ -885,9 +894,15 @@ int sre2_timing_read(sre2_ctx* ctx, double* ms, int64_t* launches) {
 int sre2_chunking(sre2_ctx* ctx, int N, int form, int64_t* shifts_per_chunk, int* groups) {
     if (!ctx || !shifts_per_chunk || !groups || N < 1 || N > SRE2_MAX_N || !form_ok(form))
         return SRE2_EINVAL;
+    const int64_t n = int64_t(1) << N;
+    // on chip, or all but shift 0 of it: no chunks
+    if (two_pass_shifts(N, form, nullptr, 0, n) < n) {
+        *shifts_per_chunk = 0;
+        *groups = 1;
+        return SRE2_OK;
+    }
     // the chunks of the high shifts x >= 2^L, most of an evaluation
     SlabRange rg[2];
-    const int64_t n = int64_t(1) << N;
     const int nr = slab_ranges(N, form, high_slab(N, form, ctx->row_pairs, nullptr), 0, n, rg);
     const Chunking ch = chunking(N, form, rg[nr - 1].slab, n, ctx->scratch_limit);
     *shifts_per_chunk = ch.cs;
@@ -899,7 +914,7 @@ int64_t sre2_half_slab_first_shift(int N, int form) {
     if (N < 1 || N > SRE2_MAX_N || !form_ok(form)) return -1;
     if (N > (is_f64(form) ? max_n<double>() : max_n<float>())) return -1;
     const int64_t n = int64_t(1) << N;
-    if (N <= fused_max(form)) return n;
+    if (!takes_slab(N, form)) return n;
     SlabRange rg[2];
     const int nr = slab_ranges(N, form, high_slab(N, form, true, nullptr), 0, n, rg);
     return rg[nr - 1].slab == kSlabFull ? n : rg[nr - 1].x0;
