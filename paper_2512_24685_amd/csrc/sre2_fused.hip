@@ -56,12 +56,6 @@ __global__ __launch_bounds__(64) void k_tiny(const typename CT<Real>::T* __restr
     S_out[idx] = s;
 }
 
-// Fused tiles that hold one shift and keep psi[k] in registers (see k_fused).
-template <typename Real>
-__host__ __device__ constexpr bool fused_keeps_psi(int NT, bool herm) {
-    return sizeof(Real) == 4 && !herm && fused_tb<Real>(NT) == NT;
-}
-
 // ---------------------------------------------------------------------------
 // Fused: whole transforms of NT bits in a 2^TB tile of SPT = 2^(TB-NT) shifts.
 // From N = 10 on only the split forms take it (FP16 up to 12 and for shift 0,
@@ -78,11 +72,7 @@ __host__ __device__ constexpr bool fused_keeps_psi(int NT, bool herm) {
 // ---------------------------------------------------------------------------
 template <typename Real, int NT, int TB, int RB, bool HERM, int SPLIT, bool GEN, typename PackT>
 __global__ __launch_bounds__(1 << (TB - RB))
-__attribute__((amdgpu_waves_per_eu(SPLIT ? SRE2_FUSEDS_WAVES
-                                   : (fused_half<Real>(NT)
-                                          ? (sizeof(Real) == 4 ? SRE2_F32_FUSEDH_WAVES
-                                                               : SRE2_FUSEDH_WAVES)
-                                          : SRE2_FUSED_WAVES))))
+__attribute__((amdgpu_waves_per_eu(SPLIT ? SRE2_FUSEDS_WAVES : SRE2_FUSED_WAVES)))
 void k_fused(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int64_t x_count,
              double* __restrict__ S_out, const int* __restrict__ scale_exp,
              const PackT pk, const Spec sp) {
@@ -116,15 +106,14 @@ void k_fused(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int6
     const Real sc = SPLIT ? ldexpf(1.0f, se) : Real(1);
     const double unscale = SPLIT ? ldexp(1.0, -4 * se) : 1.0;
     const int64_t ntiles = (x_count + SPT - 1) / SPT;
-    // one shift per tile: k = e = base | r (disjoint bits) does not depend on
-    // the tile, so FP32 tiles read psi[k] once per workgroup and keep it in
-    // registers over the tiles the workgroup takes (FP64 tiles have no
-    // registers left for it)
-    constexpr bool ONE = SPT == 1 && !HERM;
-    constexpr bool KEEP = fused_keeps_psi<Real>(NT, HERM);
+    // one shift per tile (the split forms from N = 12 on): k = e = base | r
+    // (disjoint bits) does not depend on the tile, so psi[k] is read once per
+    // workgroup and kept in registers over the tiles the workgroup takes
+    constexpr bool ONE = SPT == 1;
+    static_assert(!ONE || (sizeof(Real) == 4 && !HERM), "the half transforms take the others");
     const auto rs = buf_rsrc(psi, (uint32_t)sizeof(C) << (NT + (HERM ? 1 : 0)));
-    C psik[KEEP ? (1 << RB) : 1];
-    if constexpr (KEEP) {
+    C psik[ONE ? (1 << RB) : 1];
+    if constexpr (ONE) {
         const uint32_t base = thread_base<r0.lperm, r0.wave>();
 #pragma unroll
         for (int i = 0; i < (1 << RB); ++i) psik[i] = load_at<C>(rs, base, pdep((uint32_t)i, r0.reg));
@@ -141,28 +130,11 @@ void k_fused(const typename CT<Real>::T* __restrict__ psi, int64_t x_begin, int6
 #pragma unroll
             for (int i = 0; i < (1 << RB); ++i) {
                 const uint32_t r = pdep((uint32_t)i, r0.reg);
-                v[i] = cmul_conj_a(load_at<C>(rs, vb, r ^ xr),
-                                   KEEP ? psik[KEEP ? i : 0] : load_at<C>(rs, base, r));
+                v[i] = cmul_conj_a(load_at<C>(rs, vb, r ^ xr), psik[i]);
                 if constexpr (SPLIT) {
                     v[i].x *= sc;
                     v[i].y *= sc;
                 }
-            }
-        } else if constexpr (SPT == 1 && HERM) {
-            // one shift per tile, k = insert0(e, hb), hb the top set bit of x:
-            // insert0 maps disjoint bits to disjoint bits, so k = kb + kr with
-            // kb = insert0(base, hb) and kr = insert0(r, hb), and k ^ x splits
-            // the same way over R = insert0(REG, hb): the per-element parts
-            // stay uniform
-            const uint32_t x = (uint32_t)x0;
-            const uint32_t hb = 31u - __clz(x);
-            const uint32_t R = insert0(r0.reg, hb);
-            const uint32_t kb = insert0(thread_base<r0.lperm, r0.wave>(), hb);
-            const uint32_t vb = kb ^ (x & ~R), xr = x & R;
-#pragma unroll
-            for (int i = 0; i < (1 << RB); ++i) {
-                const uint32_t kr = insert0(pdep((uint32_t)i, r0.reg), hb);
-                v[i] = cmul_conj_a(load_at<C>(rs, vb, kr ^ xr), load_at<C>(rs, kb, kr));
             }
         } else {
             const uint32_t base = thread_base<r0.lperm, r0.wave>();
@@ -252,12 +224,13 @@ hipError_t launch_fused_nt(const void* psi, int64_t x0, int64_t xc, double* S, c
     constexpr int TB = fused_tb<Real>(NT), RB = fused_rb<Real>(NT, SPLIT != 0);
     constexpr int SPT = 1 << (TB - NT);
     const int64_t ntiles = (xc + SPT - 1) / SPT;
-    // Tiles that keep psi[k] in registers amortise its reads over the tiles a
-    // workgroup takes: their grid is twice the workgroups the GPU holds at
-    // once (queried once per kernel; measured at N = 14, 0.58 -> 0.44 ms),
-    // the others take one tile per workgroup up to 65536 workgroups.
+    // Tiles of one shift keep psi[k] in registers, which amortises its reads over
+    // the tiles a workgroup takes: their grid is twice the workgroups the GPU holds
+    // at once (queried once per kernel; whole tiles of N = 14 took 0.58 ms with
+    // one tile per workgroup, 0.44 so), the others take one tile per workgroup up
+    // to 65536 workgroups.
     int64_t cap = 65536;
-    if constexpr (fused_keeps_psi<Real>(NT, HERM)) {
+    if constexpr (SPT == 1) {
         static const int64_t resident = resident_workgroups(
             reinterpret_cast<const void*>(&k_fused<Real, NT, TB, RB, HERM, SPLIT, GEN, NoPack>),
             1 << (TB - RB));

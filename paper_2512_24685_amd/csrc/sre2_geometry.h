@@ -127,8 +127,7 @@ constexpr int row_bits_of(int NS) {
 // Two-pass tiles above 64 KiB (2^14 complex64, 2^13 complex128) transpose
 // through half the LDS (make_plan_half, make_split_plan_half), so that two
 // workgroups fit a CU; pass 1 then takes one more register bit per thread, so
-// that the round count stays that of the smaller tile.  Fused tiles: see
-// fused_half.
+// that the round count stays that of the smaller tile.
 #ifndef SRE2_HALF_ABOVE
 #define SRE2_HALF_ABOVE 65536  // bytes of a tile above which it goes half-LDS
 #endif
@@ -149,35 +148,17 @@ template <typename Real>
 constexpr int fused_tb(int N) {
     return N > Tune<Real>::FMIN ? N : Tune<Real>::FMIN;
 }
-// Half-LDS fused tiles (plain forms) take SRE2_FUSED_HALF_RB more register
-// bits per thread.  Measured on the largest tiles: the FP64 one (2^13) runs
-// 1.7x faster so; the FP32 one (2^14, 64 values per thread) spills at the
-// 256 registers that two workgroups per CU leave and runs 1.7x slower, so it
-// keeps its full tile.
-#ifndef SRE2_F32_FUSED_HALF
-#define SRE2_F32_FUSED_HALF 0
-#endif
-#ifndef SRE2_F64_FUSED_HALF
-#define SRE2_F64_FUSED_HALF 1
-#endif
-#ifndef SRE2_F32_FUSED_HALF_RB
-#define SRE2_F32_FUSED_HALF_RB 1
-#endif
-#ifndef SRE2_F64_FUSED_HALF_RB
-#define SRE2_F64_FUSED_HALF_RB 1
-#endif
+// No fused tile transposes through half the LDS: only the split forms hold tiles
+// of more than 64 KiB (N = 14), whose plans have their own order; the plain
+// forms of such sizes run as half transforms.
 template <typename Real>
-constexpr bool fused_half(int N) {
-    return (sizeof(Real) == 4 ? SRE2_F32_FUSED_HALF : SRE2_F64_FUSED_HALF) &&
-           half_lds<Real>(fused_tb<Real>(N)) && N == fused_tb<Real>(N);
+constexpr bool fused_half(int) {
+    return false;
 }
-// Registers (log2) per fused thread for transforms of N bits.
+// Registers (log2) per fused thread.
 template <typename Real>
-constexpr int fused_rb(int N, bool split) {
-    return Tune<Real>::RBF +
-           (!split && fused_half<Real>(N)
-                ? (sizeof(Real) == 4 ? SRE2_F32_FUSED_HALF_RB : SRE2_F64_FUSED_HALF_RB)
-                : 0);
+constexpr int fused_rb(int, bool) {
+    return Tune<Real>::RBF;
 }
 // Registers (log2 of complex values) per thread of a half transform: eight at
 // N = 10 (a whole wave; a pack of ten states 24 -> 12 us).  FP32: 16

@@ -177,17 +177,37 @@ hipError_t launch_pass2_ht(const void* scratch, int NS, int cs, int P, double* p
     return hipGetLastError();
 }
 
+// Row bits of the smallest size that takes two passes: N = HMAX + 1 (the FP32
+// histogram from half_hist_max + 1, the split forms' full slabs from FMAX + 1, for
+// shift 0 at least; BF16 half slabs from kImagesMaxN + 1).
+template <typename Real, int HALF, int SPLIT, bool GEN>
+constexpr int pass2_min_rows() {
+    using T = Tune<Real>;
+    int N = T::HMAX + 1;
+    if (GEN) N = half_hist_max<Real>() + 1;
+    if (SPLIT) N = HALF == HALF_NONE ? T::FMAX + 1 : SPLIT == 2 ? kImagesMaxN + 1 : T::HMAX + 1;
+    return N - T::ROW - (HALF == HALF_NONE ? 0 : 1);
+}
+
 template <typename Real, int HALF, int SPLIT, bool GEN, int... Hs>
-hipError_t dispatch_pass2(int HT, const void* scratch, int NS, int cs, int P, double* part,
-                          const int* se, const Spec& sp, int64_t x0, hipStream_t st,
-                          std::integer_sequence<int, Hs...>) {
+hipError_t dispatch_pass2_of(int HT, const void* scratch, int NS, int cs, int P, double* part,
+                             const int* se, const Spec& sp, int64_t x0, hipStream_t st,
+                             std::integer_sequence<int, Hs...>) {
+    constexpr int H0 = pass2_min_rows<Real, HALF, SPLIT, GEN>();
     hipError_t e = hipErrorInvalidValue;
-    ((HT == Hs + 1 ? (e = launch_pass2_ht<Real, Hs + 1, HALF, SPLIT, GEN>(scratch, NS, cs, P, part,
-                                                                          se, sp, x0, st),
-                      0)
-                   : 0),
+    ((HT == Hs + H0 ? (e = launch_pass2_ht<Real, Hs + H0, HALF, SPLIT, GEN>(
+                           scratch, NS, cs, P, part, se, sp, x0, st),
+                       0)
+                    : 0),
      ...);
     return e;
+}
+template <typename Real, int HALF, int SPLIT, bool GEN>
+hipError_t dispatch_pass2(int HT, const void* scratch, int NS, int cs, int P, double* part,
+                          const int* se, const Spec& sp, int64_t x0, hipStream_t st) {
+    constexpr int n = pass2_max_rows<Real>() - pass2_min_rows<Real, HALF, SPLIT, GEN>() + 1;
+    return dispatch_pass2_of<Real, HALF, SPLIT, GEN>(HT, scratch, NS, cs, P, part, se, sp, x0, st,
+                                                     std::make_integer_sequence<int, n>{});
 }
 
 }  // namespace
@@ -224,8 +244,6 @@ hipError_t launch_pass2(const void* scratch, int N, int slab, int split, int64_t
     if (slab == kSlabImages) return launch_pass2_images(scratch, N, x0, cs, P, part, se, st);
     const bool half = slab == kSlabHerm || slab == kSlabPairs;
     const int HT = NS - L - (slab == kSlabBoth ? 1 : 0);
-    constexpr int HMAX = pass2_max_rows<Real>();
-    constexpr auto hs = std::make_integer_sequence<int, HMAX>{};
     if (sp) {
         if (split || sp->kind < kRedPow || sp->kind > kRedHist ||
             (sp->kind == kRedHist && (!sp->hist || !sp->nrm || sp->nbins < 2 ||
@@ -233,31 +251,29 @@ hipError_t launch_pass2(const void* scratch, int N, int slab, int split, int64_t
             return hipErrorInvalidValue;
         if (half)
             return dispatch_pass2<Real, HALF_SLAB, 0, true>(HT, scratch, NS, cs, P, part, se, *sp,
-                                                            x0, st, hs);
-        return dispatch_pass2<Real, HALF_NONE, 0, true>(HT, scratch, NS, cs, P, part, se, *sp, x0,
-                                                        st, hs);
+                                                            x0, st);
+        return dispatch_pass2<Real, HALF_NONE, 0, true>(HT, scratch, NS, cs, P, part, se, *sp, x0, st);
     }
     const Spec none{};
     if constexpr (sizeof(Real) == 4) {
         if (split == 1)
             return half ? dispatch_pass2<Real, HALF_SLAB, 1, false>(HT, scratch, NS, cs, P, part,
-                                                                    se, none, x0, st, hs)
+                                                                    se, none, x0, st)
                         : dispatch_pass2<Real, HALF_NONE, 1, false>(HT, scratch, NS, cs, P, part,
-                                                                    se, none, x0, st, hs);
+                                                                    se, none, x0, st);
         if (split == 2)
             return half ? dispatch_pass2<Real, HALF_SLAB, 2, false>(HT, scratch, NS, cs, P, part,
-                                                                    se, none, x0, st, hs)
+                                                                    se, none, x0, st)
                         : dispatch_pass2<Real, HALF_NONE, 2, false>(HT, scratch, NS, cs, P, part,
-                                                                    se, none, x0, st, hs);
+                                                                    se, none, x0, st);
     }
     if (half)
         return dispatch_pass2<Real, HALF_SLAB, 0, false>(HT, scratch, NS, cs, P, part, se, none,
-                                                         x0, st, hs);
+                                                         x0, st);
     if (slab == kSlabBoth)
         return dispatch_pass2<Real, HALF_BOTH, 0, false>(HT, scratch, NS, cs, P, part, se, none,
-                                                         x0, st, hs);
-    return dispatch_pass2<Real, HALF_NONE, 0, false>(HT, scratch, NS, cs, P, part, se, none, x0,
-                                                     st, hs);
+                                                         x0, st);
+    return dispatch_pass2<Real, HALF_NONE, 0, false>(HT, scratch, NS, cs, P, part, se, none, x0, st);
 }
 
 template hipError_t launch_pass2<float>(const void*, int, int, int, int64_t, int, int, double*,

@@ -39,16 +39,9 @@ namespace sre2 {
 #ifndef SRE2_FUSEDS_WAVES
 #define SRE2_FUSEDS_WAVES 2
 #endif
-// Half-LDS tiles: two workgroups share a CU.  Two-pass tiles ask for the
-// waves per SIMD that takes (half_waves: four for 512-thread FP32 tiles, i.e.
-// at most 128 registers, two for 256-thread FP64 tiles); the half-LDS fused
-// tile (256 threads of 64 values) needs two waves per SIMD.
-#ifndef SRE2_FUSEDH_WAVES
-#define SRE2_FUSEDH_WAVES 2
-#endif
-#ifndef SRE2_F32_FUSEDH_WAVES
-#define SRE2_F32_FUSEDH_WAVES SRE2_FUSEDH_WAVES
-#endif
+// Half-LDS tiles: two workgroups share a CU.  They ask for the waves per SIMD
+// that takes (half_waves: four for 512-thread FP32 tiles, i.e. at most 128
+// registers, two for 256-thread FP64 tiles).
 #ifndef SRE2_HALF_WGS
 #define SRE2_HALF_WGS 2  // workgroups per CU that half-LDS two-pass tiles aim for
 #endif
@@ -66,8 +59,7 @@ __host__ __device__ constexpr int half_waves(int tb, int rb) {
 //                   halves; one plan for both), with H_16 factors on the
 //                   matrix cores (pass 1 ends with a round whose lanes run
 //                   over the lowest bits, for the stores)
-//   tiles above 64 KiB (half_lds) take half-LDS plans (not the fused split
-//   form); the fused kernel's then hold 64 values per thread
+//   two-pass tiles above 64 KiB (half_lds) take half-LDS plans
 template <typename Real, int TB, int RB, int PK>
 __host__ __device__ constexpr Plan plan_of() {
     constexpr int SB = Prec<Real>::SB;
@@ -86,8 +78,7 @@ __host__ __device__ constexpr Plan plan_of() {
         return H ? make_plan_half(TB, RB, SB, TB - (PK - 3000))
                  : make_plan(TB, RB, SB, TB - (PK - 3000), TB);
     if (PK >= 2000) return H ? make_plan_half(TB, RB, SB, 0) : make_plan(TB, RB, SB, 0, TB);
-    return fused_half<Real>(PK - 1000) ? make_plan_half(TB, RB, SB, 0)
-                                       : make_plan(TB, RB, SB, 0, PK - 1000);
+    return make_plan(TB, RB, SB, 0, PK - 1000);
 }
 
 template <int TB, int RB, int PK>
