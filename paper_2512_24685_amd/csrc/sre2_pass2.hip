@@ -252,7 +252,8 @@ hipError_t launch_pass2(const void* scratch, int N, int slab, int split, int64_t
         if (half)
             return dispatch_pass2<Real, HALF_SLAB, 0, true>(HT, scratch, NS, cs, P, part, se, *sp,
                                                             x0, st);
-        return dispatch_pass2<Real, HALF_NONE, 0, true>(HT, scratch, NS, cs, P, part, se, *sp, x0, st);
+        return dispatch_pass2<Real, HALF_NONE, 0, true>(HT, scratch, NS, cs, P, part, se, *sp, x0,
+                                                        st);
     }
     const Spec none{};
     if constexpr (sizeof(Real) == 4) {
@@ -273,7 +274,8 @@ hipError_t launch_pass2(const void* scratch, int N, int slab, int split, int64_t
     if (slab == kSlabBoth)
         return dispatch_pass2<Real, HALF_BOTH, 0, false>(HT, scratch, NS, cs, P, part, se, none,
                                                          x0, st);
-    return dispatch_pass2<Real, HALF_NONE, 0, false>(HT, scratch, NS, cs, P, part, se, none, x0, st);
+    return dispatch_pass2<Real, HALF_NONE, 0, false>(HT, scratch, NS, cs, P, part, se, none, x0,
+                                                     st);
 }
 
 template hipError_t launch_pass2<float>(const void*, int, int, int, int64_t, int, int, double*,

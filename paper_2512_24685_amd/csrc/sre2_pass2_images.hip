@@ -7,10 +7,11 @@
 // images_rows) clear, and this kernel rebuilds the others by sign flips.  The
 // other forms transform the stored rows alone (k_pass2, HALF_SLAB; on chip,
 // k_half), which gives the same values up to rounding at half the work.  With
-// 16 significant bits that rounding is 2 to 4e-9 of the S_x of N = 15 and 16
-// (2-norm, shift 0 among them), more than results may move between versions
-// of the library (1e-9); from N = 17 on, where S_x average over more values
-// (6.5e-10), the BF16 form takes the half slabs too.
+// 16 significant bits that rounding would move the S_x of N = 15 and 16 by 2 to 4e-9
+// (2-norm, shift 0 among them).  That is far inside the form's error bar, but
+// sre2.h says that these sizes keep the bits of the rebuilt rows; from N = 17
+// on, where S_x average over more values (6.5e-10), the BF16 form takes the
+// half slabs too.
 //
 // j is taken among the register row bits when xh has one, so that which
 // elements are rebuilt is fixed per register index (pair_load_reg); otherwise
